@@ -16,18 +16,22 @@
 // source's transform is shared by every target that sees it (up to 27 parents' blocks), so what
 // remains per pair is the pointwise product, C^2 (N_g + 1) complex multiply-adds.
 //
+// Stored order of a spectrum's modes: kz fastest, then kx, then ky (mode k = (ky HC + kx) C + kz), so
+// that the transforms' z passes handle whole runs. FP32 rows are interleaved (re, im); FP64 rows
+// hold two real parts, then their two imaginary parts (16 bytes each), as the FP64 product kernel
+// loads them.
+//
 // Kernels:
-//   k_cells_forward   one wave per source gridlet (cells of levels >= 2 and virtual cubes):
-//                     half spectrum [kz < C][ky < C][kx <= N_g] by separable direct sums.
-//   k_cells_accum     one thread per (parent, mode), one launch per parent level. The Green table
-//                     of the level is shared by every parent, so a workgroup stages its chunk of
-//                     modes in LDS and runs several parents side by side; the 8 children of a
-//                     parent share the 6^3 block of sources, so for each source plane bz a
-//                     thread keeps that plane's 36 spectra in registers and applies each Green
-//                     entry to every child and slot it joins (up to 4 of them). Only the split
-//                     parents are visited, from a list built with the tree.
-//   k_cells_inverse   one workgroup per target: pruned inverse (z, then y, then the Hermitian x
-//                     sum), the N_g^3 corner written as the target's gridlet potentials. The
+//   k_cells_forward   several source gridlets (cells of levels >= 2 and virtual cubes) per
+//                     workgroup: half spectrum [kz < C][ky < C][kx <= N_g] by separable direct
+//                     sums, one line per thread.
+//   k_cells_accum_f32, k_cells_accum_f64
+//                     the products on the matrix cores: for one mode, the 8 children's sums over
+//                     the 216 block slots are a matrix product, child x slot (Green values, the
+//                     same for every parent of a level) times slot x parent (spectra). One launch
+//                     for all levels.
+//   k_cells_inverse   several targets per workgroup: pruned inverse (z, then y, then the Hermitian
+//                     x sum), the N_g^3 corner written as the target's gridlet potentials. The
 //                     inverse runs in double whatever the plan's precision (it is a small part of
 //                     the work); in FP32 plans the result is stored as its mean (double) plus the
 //                     zero-mean gridlet, so that the large common value of a target's potentials
@@ -56,15 +60,10 @@ struct CellShape {
   static constexpr int OFFS = 343;          // d in [-3, 3]^3, index (dx+3) + 7 (dy+3) + 49 (dz+3)
 };
 
-// e^{sign 2 pi i j / C} for j < C, in LDS (double sincospi, rounded once to T)
-template <typename T, int C>
-__device__ __forceinline__ void load_twiddles(cplx<T>* tw, double sign) {
-  const int j = threadIdx.x;
-  if (j < C) {
-    double s, c;
-    sincospi(2.0 * j / C, &s, &c);
-    tw[j] = {T(c), T(sign * s)};
-  }
+// place of mode k, part c (0 real, 1 imaginary), in a stored row of reals
+template <typename T>
+__host__ __device__ constexpr int mode_pos(int k, int c) {
+  return sizeof(T) == 4 ? 2 * k + c : (k / 2) * 4 + c * 2 + k % 2;
 }
 
 template <typename T>
@@ -72,31 +71,33 @@ struct CellArgs {
   int first_cell;    // id of the first cell of level 2: sources and targets are indexed from it
   int nsources;      // cells of levels >= 2, then the virtual cubes (row nsources of the
                      // source spectra is zero)
+  int ntargets;
   int first_parent;  // first row of the block table (cells of level 1)
-  int nlevels;
-  const int* level_off;
   const int* child8;
   const int* blocks;
   const T* gridlet;
   T* local;
-  const cplx<T>* gcell;  // [level - 2][343][K]
-  cplx<T>* sspec;        // [source - first_cell][K]
-  cplx<T>* tspec;        // [target - first_cell][K]
-  double* m2l_mean;      // [cells]: mean of each target's result, FP32 plans
+  const T* gcell;    // [level - 2][343][2 KP]
+  T* sspec;          // [source - first_cell][2 KP]
+  T* tspec;          // [target - first_cell][2 KP]
+  double* m2l_mean;  // [cells]: mean of each target's result, FP32 plans
 };
 
-// One wave per source (kFwdSources per workgroup; packing four measured slower than one). Each
-// pass gives every
-// lane whole lines: a lane loads the N_g nonzero samples of its line into registers and forms
-// all the line's outputs with compile-time twiddles (exp(-2 pi i jk / C) as immediates), so no
-// output waits on a chain of table loads. Sums run over the samples in order, as the separable
-// definition reads.
-constexpr int kFwdSources = 1;
-constexpr int kFwdThreads = 64 * kFwdSources;
+constexpr int kCellThreads = 256;
 
-// out[k] = sum_j v[j] w^{jk}, w = exp(-2 pi i / C), for the K outputs of one line
-template <typename T, int NG, int C, int K, bool REAL_IN>
-__device__ __forceinline__ void line_dft(const cplx<T> (&v)[NG], cplx<T>* out, int stride) {
+// Gridlets per workgroup of the forward and inverse transforms: as many as keep one column
+// (ky, kx) per thread, which is the widest pass of either (3 at N_g = 6: 252 of 256 threads).
+template <int NG, int EXT>
+constexpr int cells_per_group() {
+  using S = CellShape<NG, EXT>;
+  constexpr int t = kCellThreads / (S::C * S::HC);
+  return t > 16 ? 16 : t;
+}
+
+// out_k = sum_j v[j] w^{jk}, w = exp(SIGN 2 pi i / C), for the C outputs k < K of one line, in order,
+// handed to put(k, value). Compile-time twiddles: no output waits on a chain of table loads.
+template <typename T, int NG, int C, int K, bool REAL_IN, typename F>
+__device__ __forceinline__ void line_dft(const cplx<T> (&v)[NG], F&& put) {
   static_for<0, K>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     cplx<T> acc = {T(0), T(0)};
@@ -110,251 +111,635 @@ __device__ __forceinline__ void line_dft(const cplx<T> (&v)[NG], cplx<T>* out, i
         acc = cadd(acc, cmul(v[j], cplx<T>{wr, wi}));
       }
     });
-    out[k * stride] = acc;
+    put(kc, acc);
   });
 }
 
+// The kernel writes KP complex values for the N_g^3 it reads, so its floor is the write (2^24
+// clustered particles, N_g = 4, FP32: 7.6 GB in 1.62 ms, 1.90 ms with a wave per source). The z pass
+// keeps its outputs in registers until the whole workgroup has read the y pass's, then assembles
+// the stored rows in the same LDS and copies them out 16 bytes per lane in order: every line is
+// written whole, by one instruction.
 template <typename T, int NG, int EXT>
-__global__ __launch_bounds__(kFwdThreads) void k_cells_forward(CellArgs<T> a) {
+__global__ __launch_bounds__(kCellThreads) void k_cells_forward(CellArgs<T> a) {
   using S = CellShape<NG, EXT>;
   constexpr int C = S::C, HC = S::HC, K = S::K, KP = S::KP, M = S::M;
-  __shared__ T s_gw[kFwdSources][M];
-  __shared__ cplx<T> s_a1w[kFwdSources][NG * NG * HC];  // [z][y][kx]
-  __shared__ cplx<T> s_a2w[kFwdSources][NG * C * HC];   // [z][ky][kx]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int src = blockIdx.x * kFwdSources + wave;
-  // every wave passes every barrier; only waves with a source of their own do its work
-  const bool zero_row = src == a.nsources, work = src < a.nsources;
-  T* s_g = s_gw[wave];
-  cplx<T>* s_a1 = s_a1w[wave];
-  cplx<T>* s_a2 = s_a2w[wave];
-  cplx<T>* out = a.sspec + size_t(src) * KP;
-  if (zero_row)  // the zero row that empty block slots read
-    for (int e = lane; e < KP; e += 64) out[e] = {T(0), T(0)};
-  if (work) {
-    const T* g = a.gridlet + size_t(a.first_cell + src) * M;
-    for (int e = lane; e < M; e += 64) s_g[e] = g[e];
+  constexpr int PER = cells_per_group<NG, EXT>();
+  constexpr int N1 = PER * NG * NG * HC, N2 = PER * NG * C * HC;  // complex values of the passes
+  constexpr size_t work_bytes = (N1 + N2) * sizeof(cplx<T>) + PER * M * sizeof(T);
+  constexpr size_t row_bytes = size_t(PER) * 2 * KP * sizeof(T);
+  static_assert(PER * C * HC <= kCellThreads, "one column per thread in the z pass");
+  __shared__ __align__(16) char s_mem[work_bytes > row_bytes ? work_bytes : row_bytes];
+  cplx<T>* s_a1 = reinterpret_cast<cplx<T>*>(s_mem);  // [source][z][y][kx]
+  cplx<T>* s_a2 = s_a1 + N1;                          // [source][z][ky][kx]
+  T* s_g = reinterpret_cast<T*>(s_a2 + N2);
+  T* s_row = reinterpret_cast<T*>(s_mem);             // [source][2 KP], after the z pass
+  const int tid = threadIdx.x;
+  const int src0 = blockIdx.x * PER;
+  // sources of this workgroup: src0 .. src0 + cnt - 1; row nsources is the zero row that empty
+  // block slots read
+  const int cnt = min(PER, a.nsources - src0);
+  if (src0 + PER > a.nsources) {
+    T* zero = a.sspec + size_t(a.nsources) * 2 * KP;
+    for (int e = tid; e < 2 * KP; e += kCellThreads) zero[e] = T(0);
+  }
+  if (cnt <= 0) return;
+  const T* g = a.gridlet + size_t(a.first_cell + src0) * M;
+  for (int e = tid; e < cnt * M; e += kCellThreads) s_g[e] = g[e];
+  __syncthreads();
+  // x: one real row (source, z, y) per thread, its half spectrum kx <= C/2
+  for (int r = tid; r < cnt * NG * NG; r += kCellThreads) {
+    cplx<T> v[NG];
+#pragma unroll
+    for (int x = 0; x < NG; ++x) v[x] = {s_g[r * NG + x], T(0)};
+    line_dft<T, NG, C, HC, true>(v, [&](auto kc, cplx<T> o) { s_a1[r * HC + decltype(kc)::value] = o; });
   }
   __syncthreads();
-  // x: one real row (z, y) per lane, its half spectrum kx <= C/2
-  if (work) {
-    for (int r = lane; r < NG * NG; r += 64) {
-      cplx<T> v[NG];
+  // y: one column (source, z, kx) per thread, all C values of ky
+  for (int q = tid; q < cnt * NG * HC; q += kCellThreads) {
+    const int z = q / HC, kx = q % HC;  // z: (source, z)
+    cplx<T> v[NG];
 #pragma unroll
-      for (int x = 0; x < NG; ++x) v[x] = {s_g[r * NG + x], T(0)};
-      line_dft<T, NG, C, HC, true>(v, s_a1 + r * HC, 1);
+    for (int y = 0; y < NG; ++y) v[y] = s_a1[(z * NG + y) * HC + kx];
+    line_dft<T, NG, C, C, false>(
+        v, [&](auto kc, cplx<T> o) { s_a2[(z * C + decltype(kc)::value) * HC + kx] = o; });
+  }
+  __syncthreads();
+  // z: one column (source, ky, kx) per thread, all C values of kz
+  const bool live = tid < cnt * C * HC;
+  const int sl = tid / (C * HC), col = tid % (C * HC);
+  cplx<T> out[C];
+  if (live) {
+    cplx<T> v[NG];
+#pragma unroll
+    for (int z = 0; z < NG; ++z) v[z] = s_a2[(sl * NG + z) * C * HC + col];
+    line_dft<T, NG, C, C, false>(v, [&](auto kc, cplx<T> o) { out[decltype(kc)::value] = o; });
+  }
+  __syncthreads();  // the y pass's values are consumed
+  if (live) {
+    T* row = s_row + sl * 2 * KP;
+#pragma unroll
+    for (int kz = 0; kz < C; ++kz) {
+      row[mode_pos<T>(col * C + kz, 0)] = out[kz].re;
+      row[mode_pos<T>(col * C + kz, 1)] = out[kz].im;
+    }
+  }
+  if constexpr (KP > K) {
+    for (int e = tid; e < cnt * (KP - K); e += kCellThreads) {
+      T* row = s_row + (e / (KP - K)) * 2 * KP;
+      row[mode_pos<T>(K + e % (KP - K), 0)] = T(0);
+      row[mode_pos<T>(K + e % (KP - K), 1)] = T(0);
     }
   }
   __syncthreads();
-  // y: one column (z, kx) per lane, all C values of ky
-  if (work) {
-    for (int q = lane; q < NG * HC; q += 64) {
-      const int z = q / HC, kx = q % HC;
-      cplx<T> v[NG];
-#pragma unroll
-      for (int y = 0; y < NG; ++y) v[y] = s_a1[(z * NG + y) * HC + kx];
-      line_dft<T, NG, C, C, false>(v, s_a2 + z * C * HC + kx, HC);
+  constexpr int PIECES = 2 * KP * int(sizeof(T)) / 16;  // 16-byte pieces of a row
+  const float4* from = reinterpret_cast<const float4*>(s_row);
+  float4* to = reinterpret_cast<float4*>(a.sspec + size_t(src0) * 2 * KP);
+  for (int e = tid; e < cnt * PIECES; e += kCellThreads) to[e] = from[e];
+}
+
+// ---------------------------------------------------------------------------------------------
+// Products on the matrix cores. For one mode, child c's sum over the block slots s of its parent is
+// T_c = sum_s G(d(c, s)) S_s (complex; G = 0 for the near offsets and d = slot - 2 - child per
+// axis, so the Green values depend on (c, s) alone and serve every parent of the level). 189 of the
+// 216 slots carry work, so 88% of the matrix work is wanted.
+//
+// A workgroup takes a tile of split parents of one level and a chunk of modes (32 in FP32, 8 in FP64),
+// whose Green values it keeps in LDS (88 or 44 KB). Workgroups are persistent; work
+// items are (chunk, tile) with the tiles of all levels fastest, one contiguous range of items per
+// XCD, taken by its workgroups in turn: those in flight share a chunk and neighbouring parents,
+// whose source rows overlap in the XCD's L2.
+// ---------------------------------------------------------------------------------------------
+// threads of a workgroup and its parents, 8 per wave; resident workgroups per CU (two waves per SIMD)
+template <typename T, bool CENTRAL>
+constexpr int kAccumThreads = sizeof(T) == 4 && !CENTRAL ? 512 : 256;
+template <typename T, bool CENTRAL>
+constexpr int kTileParents = kAccumThreads<T, CENTRAL> / 8;
+template <typename T, bool CENTRAL>
+constexpr int kAccumPerCU = 512 / kAccumThreads<T, CENTRAL>;
+template <typename T>
+constexpr int kChunkModes = sizeof(T) == 4 ? 32 : 8;
+
+struct TileTable {
+  int ntiles;                       // tiles of all parent levels
+  int first[kMaxLevelsHost + 1];    // first tile of parent level l (ntiles past the last)
+  int pbeg[kMaxLevelsHost + 1];     // first list entry of parent level l
+};
+
+// The work items of this workgroup: it = begin; it < end; it += step. A few items per workgroup are
+// taken in order, so that a chunk's Green values are staged once for consecutive tiles; many are
+// taken in turn by the XCD's workgroups.
+struct Items {
+  int begin, end, step;
+  __device__ __forceinline__ explicit Items(int total) {
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, per = gridDim.x >> 3;
+    const int first = int((int64_t(total) * xcd) / 8), last = int((int64_t(total) * (xcd + 1)) / 8);
+    if (last - first <= 8 * per) {
+      begin = first + int((int64_t(last - first) * j) / per);
+      end = first + int((int64_t(last - first) * (j + 1)) / per);
+      step = 1;
+    } else {
+      begin = first + j;
+      end = last;
+      step = per;
     }
   }
-  __syncthreads();
-  // z: one column (ky, kx) per lane, all C values of kz, written to the source's spectrum row
-  if (work) {
-    for (int e = K + lane; e < KP; e += 64) out[e] = {T(0), T(0)};
-    for (int col = lane; col < C * HC; col += 64) {
-      cplx<T> v[NG];
+};
+
+// of an item its chunk, its parents' level lp, its first list entry p0 and its number of parents pn
+template <int TILE>
+__device__ __forceinline__ void item_of(const TileTable& tt, int it, int& chunk, int& lp, int& p0,
+                                        int& pn) {
+  chunk = it / tt.ntiles;
+  const int tile = it % tt.ntiles;
+  lp = 1;
+  while (lp + 1 < kMaxLevelsHost && tile >= tt.first[lp + 1]) ++lp;
+  p0 = tt.pbeg[lp] + (tile - tt.first[lp]) * TILE;
+  pn = min(TILE, tt.pbeg[lp + 1] - p0);
+}
+
+// staged offsets: all 7^3 (|d| <= 3), or for the central cubes the 5^3 with |d| <= 2
+template <bool CENTRAL>
+struct AccumShape {
+  static constexpr int OW = CENTRAL ? 5 : 7, OR = OW / 2, NOFF = OW * OW * OW;
+  static constexpr int B0 = CENTRAL ? 1 : 0, NB = CENTRAL ? 4 : 6;  // first block coordinate, count
+};
+
+// Each wave takes 8 of the tile's parents and all modes of the chunk, and steps through the slots. The
+// spectra go from memory to the wave's own LDS rows in whole lines (consecutive lanes per line: a
+// lane per parent and mode, the operand layout, costs the vector cache one access per lane, which
+// bounded a version without the LDS rows at 40% matrix utilization). The steps are pipelined: while
+// one's products run, later ones' loads are in flight, and in FP32 the next one's operands are read
+// from LDS and the rows of the one after it written there (two buffers). No barrier in the loop, since a
+// wave's LDS operations execute in order. LDS serves 16 lanes x 16 bytes per cycle from 64 banks;
+// both operands' rows are swizzled in 16-byte pieces so that the 16 lanes of a pass read all banks
+// once.
+//
+// Measured per evaluation, near zone in line, against one thread per (parent, mode) on the vector
+// ALU, one launch per level: 2^24 clustered particles (N_g = 4, FP32) 21.1 -> 14.0 ms (70 TFLOP/s of
+// matrix work, 49% of the cycles); 10^6 clustered, extended N_g = 6, FP32 3.73 -> 2.27 ms; 150,001
+// Plummer, N_g = 6, FP64 0.96 -> 0.52 ms; the central cubes of 2^18 Plummer, N_g = 6, FP32
+// 0.31 -> 0.20 ms. With every source row in L2 the 2^24 case takes 13.2 ms (measured on the version
+// before the operand pipeline): what bounds it is issue beside the matrix instructions, two waves
+// per SIMD, not memory.
+
+// this wave's LDS writes before, its reads after (and the reverse), in program order
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// FP32. v_mfma_f32_4x4x1: 16 blocks (modes) of 4 children times 4 parents, one slot per
+// instruction. Each instruction is one fused multiply-add per result, so a result's terms are added
+// in slot order, real products before cross terms: the FP32 rounding of the sums (which the
+// interpolation amplifies at N_g = 6) is that of a plain loop over the slots.
+//
+// Lane l holds modes 2 (l / 4) and 2 (l / 4) + 1 of the chunk's 32 and, as an operand, child or parent
+// l % 4 of a quad; 2 x 2 quads of (children, parents) with real and imaginary parts of two modes are
+// 16 accumulators. A step is one slot; loads run one row of slots (fixed by, bz) ahead.
+template <int NG, int EXT, bool CENTRAL = false>
+__global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float, CENTRAL>)) void k_cells_accum_f32(CellArgs<float> a,
+                                                                             TileTable tt,
+                                                                             const int* plist) {
+  using S = CellShape<NG, EXT>;
+  using A = AccumShape<CENTRAL>;
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  constexpr int KP = S::KP, KC = kChunkModes<float>, NCH = (KP + KC - 1) / KC;
+  constexpr int OW = A::OW, OR = A::OR, NOFF = A::NOFF, B0 = A::B0, NB = A::NB;
+  constexpr int TILE = kTileParents<float, CENTRAL>, WP = 8;  // parents of a tile, of a wave
+  constexpr int PC = KC / 2;                         // 16-byte pieces (mode pairs) of a row
+  constexpr int NR = NB * NB;                        // rows of slots
+  __shared__ f4 s_g[NOFF * PC];                      // [offset][pieces, swizzled]
+  __shared__ f4 s_b[TILE / WP][2 * WP * PC];         // per wave: [buffer][parent][pieces, swizzled]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int mp = lane >> 2, i = lane & 3;            // mode pair, child or parent of a quad
+  const int cx = i & 1, cy = i >> 1;
+  // byte offsets into s_g of (child i of either cz, this mode pair) at slot (0, 0, 0), for slots
+  // whose bx and by have parities px and py
+  int ga[2][2];
 #pragma unroll
-      for (int z = 0; z < NG; ++z) v[z] = s_a2[z * C * HC + col];
-      line_dft<T, NG, C, C, false>(v, out + col, C * HC);
+  for (int py = 0; py < 2; ++py)
+#pragma unroll
+    for (int px = 0; px < 2; ++px) {
+      const int swz = ((1 - cx + px) & 1) | (((1 - cy + py) & 1) << 1);
+      ga[py][px] = (((1 - cx) + OW * (1 - cy)) * PC + (mp ^ (swz << 2))) * 16;
+    }
+  const char* sg = reinterpret_cast<const char*>(s_g);
+  const f4* sb = s_b[wave] + i * PC + (mp ^ (i << 2));  // parent i of either quad, this mode pair
+  // as a loader: piece lane % 16 of the parents lane / 16 and 4 + lane / 16
+  const int lpar = lane >> 4, lpiece = lane & 15;
+  f4* sw = s_b[wave] + lpar * PC + (lpiece ^ (lpar << 2));
+
+  const Items items(NCH * tt.ntiles);
+  int staged = -1;
+  for (int it = items.begin; it < items.end; it += items.step) {
+    int chunk, lp, p0, pn;
+    item_of<TILE>(tt, it, chunk, lp, p0, pn);
+    // the last chunk may be half full: its absent pieces are read as the first one and not written
+    const int pieces = min(PC, (KP - chunk * KC) / 2);
+    if (staged != chunk * kMaxLevelsHost + lp) {  // workgroup-uniform
+      staged = chunk * kMaxLevelsHost + lp;
+      __syncthreads();  // the previous item's Green values are consumed
+      // the children's level is lp + 1
+      const float* G = a.gcell + size_t(lp - 1) * S::OFFS * 2 * KP + chunk * 2 * KC;
+      for (int e = tid; e < NOFF * PC; e += kAccumThreads<float, CENTRAL>) {
+        const int o = e / PC, j = e % PC;
+        const int x = o % OW, y = (o / OW) % OW, z = o / (OW * OW);
+        const int o343 = (x + 3 - OR) + 7 * (y + 3 - OR) + 49 * (z + 3 - OR);
+        const int swz = (x & 1) | ((y & 1) << 1);
+        s_g[o * PC + (j ^ (swz << 2))] =
+            reinterpret_cast<const f4*>(G + size_t(o343) * 2 * KP)[j < pieces ? j : 0];
+      }
+      __syncthreads();
+    }
+    if (wave * WP >= pn) continue;  // wave-uniform; the barriers above are workgroup-uniform
+    // row ids: lane (parent lane / 8, bx lane % 8) holds one row of slots of its parent (the zero row
+    // for an empty slot; any valid table row for an absent parent, whose ids are not used)
+    const int ipar = wave * WP + (lane >> 3);
+    const bool have = ipar < pn;
+    const int* ids = a.blocks + size_t(plist[p0 + min(ipar, pn - 1)] - a.first_parent) * 216 + B0 * 43 +
+                     min(lane & 7, NB - 1);
+    auto load_ids = [&](int row) {
+      const int v = ids[6 * (row % NB) + 36 * (row / NB)];
+      return have && v >= 0 ? v - a.first_cell : a.nsources;
+    };
+    const float* spec = a.sspec + chunk * 2 * KC + (lpiece < pieces ? lpiece : 0) * 4;
+    f4 rows[NB][2];
+    // spectrum rows of slot bx, both of the loader's parents, from a row of ids
+    auto row_of = [&](int idv, int bx, int (&r)[2]) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) r[j] = __shfl(idv, (lpar + 4 * j) * 8 + bx, 64);
+    };
+    auto load_rows = [&](const int (&r)[2], f4 (&to)[2]) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) to[j] = *reinterpret_cast<const f4*>(spec + size_t(r[j]) * 2 * KP);
+    };
+    auto put_rows = [&](int buf, const f4 (&from)[2]) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) sw[(buf * WP + 4 * j) * PC] = from[j];
+    };
+    // Green values of slot bx of the row at gr (by of parity py), and this lane's two parents' spectra
+    auto load_slot = [&](const char* gr, int py, int bx, f4 (&g)[2], f4 (&v)[2]) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        g[c] = *reinterpret_cast<const f4*>(gr + ga[py][bx & 1] + (bx + OW * OW * (1 - c)) * (PC * 16));
+#pragma unroll
+      for (int p = 0; p < 2; ++p) v[p] = sb[((bx & 1) * WP + 4 * p) * PC];
+    };
+    auto mac = [](float x, float y, f4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(x, y, c, 0, 0, 0); };
+    f4 re[2][2][2], im[2][2][2];  // [mode][cz][parent quad]
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) re[m][c][p] = im[m][c][p] = f4{0.f, 0.f, 0.f, 0.f};
+    // ids of the rows of slots after the current one (past the last: the last one's again)
+    int id1 = load_ids(min(1, NR - 1)), id2 = load_ids(min(2, NR - 1));
+    int r[2];
+    {
+      const int id0 = load_ids(0);
+#pragma unroll
+      for (int bx = 0; bx < NB; ++bx) {
+        row_of(id0, bx, r);
+        load_rows(r, rows[bx]);
+      }
+    }
+    wave_lds_fence();
+    put_rows(0, rows[0]);
+    put_rows(1, rows[1]);
+    wave_lds_fence();
+    row_of(id1, 0, r);
+    load_rows(r, rows[0]);
+    row_of(id1, 1, r);
+    load_rows(r, rows[1]);
+    row_of(id1, 2, r);  // the next load's rows, ready before they are wanted
+    f4 g[2], v[2], gn[2], vn[2];
+    load_slot(sg, 0, 0, g, v);
+    // rows of slots in pairs, by even and odd (NB is even)
+    auto green_row = [&](int row) { return sg + (OW * (row % NB) + OW * OW * (row / NB)) * (PC * 16); };
+#pragma unroll 1
+    for (int row0 = 0; row0 < NR; row0 += 2) {
+#pragma unroll
+      for (int py = 0; py < 2; ++py) {
+        const int row = row0 + py;
+        const char* gr = green_row(row);
+        const char* gr1 = green_row(min(row + 1, NR - 1));
+        const int id3 = load_ids(min(row + 3, NR - 1));
+#pragma unroll
+        for (int bx = 0; bx < NB; ++bx) {
+          // operands of the next slot (past the last one: of some slot, not used)
+          if (bx + 1 < NB) load_slot(gr, py, bx + 1, gn, vn);
+          else load_slot(gr1, py ^ 1, 0, gn, vn);
+          wave_lds_fence();
+          // rows of the slot after it, in the buffer whose operands are in registers; their
+          // registers then take the rows one row of slots later
+          constexpr int N = NB;
+          const int k = (bx + 2) % N;
+          put_rows(bx & 1, rows[k]);
+          load_rows(r, rows[k]);
+          wave_lds_fence();
+          row_of(bx + 3 < N ? id1 : id2, (bx + 3) % N, r);
+          __builtin_amdgcn_sched_barrier(0);
+          // two rounds of 16 independent products
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+              for (int p = 0; p < 2; ++p) {
+                re[m][c][p] = mac(g[c][2 * m], v[p][2 * m], re[m][c][p]);
+                im[m][c][p] = mac(g[c][2 * m], v[p][2 * m + 1], im[m][c][p]);
+              }
+          const float ng[2][2] = {{-g[0][1], -g[0][3]}, {-g[1][1], -g[1][3]}};
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+              for (int p = 0; p < 2; ++p) {
+                re[m][c][p] = mac(ng[c][m], v[p][2 * m + 1], re[m][c][p]);
+                im[m][c][p] = mac(g[c][2 * m + 1], v[p][2 * m], im[m][c][p]);
+              }
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            g[c] = gn[c];
+            v[c] = vn[c];
+          }
+        }
+        id1 = id2;
+        id2 = id3;
+      }
+    }
+    // register r of lane l: child r of the quad, parent l % 4
+    if (mp < pieces) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int k = wave * WP + p * 4 + i;
+        const int* kids = a.child8 + size_t(plist[p0 + min(k, pn - 1)]) * 8;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int t = k < pn ? kids[4 * c + r] : -1;
+            if (t >= 0)
+              *reinterpret_cast<f4*>(a.tspec + size_t(t - a.first_cell) * 2 * KP + chunk * 2 * KC + mp * 4) =
+                  f4{re[0][c][p][r], im[0][c][p][r], re[1][c][p][r], im[1][c][p][r]};
+          }
+      }
     }
   }
 }
 
-// Mode chunk of one workgroup of k_cells_accum and the parents it runs side by side: a chunk of
-// the Green table of a level (343 offsets x KM modes) is 44 KB of LDS in either precision.
-template <typename T>
-struct AccumShape {
-  static constexpr int KM = sizeof(T) == 4 ? 16 : 8;
-  static constexpr int PP = 256 / KM;
-};
-
-// One launch per parent level; workgroup (chunk, group): modes [chunk KM, chunk KM + KM) of the
-// split parents plist[pbeg + group PP ...], one (parent, mode) per thread. CENTRAL: only the
-// sources in the central 4^3 of the block (block coordinates 1..4; the rest of every child's
-// zone comes from the transform shared by the parent's children).
-template <typename T, int NG, int EXT, bool CENTRAL = false>
-__global__ __launch_bounds__(256) void k_cells_accum(CellArgs<T> a, int tlevel, const int* plist,
-                                                     int pbeg, int pend) {
+// FP64. v_mfma_f64_16x16x4: rows (child, part of G), columns (parent, part of S), 4 slots per
+// instruction; the four real products Gr Sr, Gr Si, Gi Sr, Gi Si of 8 children and 8 parents, whose
+// parts are combined once at the end. As operands, lane l is column (or row) l % 16 and slot l / 16 of
+// a step of 2 x 2 slots (2u .. 2u + 1, 2v .. 2v + 1, bz), so every LDS address is a lane constant plus
+// an immediate, and the swizzle of the Green values, by the parities of dx and dy, is a lane constant
+// too. One LDS buffer per wave (a second one was no faster alone, 0.53 against 0.52 ms on 150,001
+// Plummer particles, and left no room for the near-zone workgroups that run beside it).
+template <int NG, int EXT, bool CENTRAL = false>
+__global__ __launch_bounds__((kAccumThreads<double, CENTRAL>), (kAccumPerCU<double, CENTRAL>)) void k_cells_accum_f64(CellArgs<double> a,
+                                                                              TileTable tt,
+                                                                              const int* plist) {
   using S = CellShape<NG, EXT>;
-  using A = AccumShape<T>;
-  constexpr int K = S::KP, KM = A::KM, PP = A::PP;  // the stored rows (zero-padded modes)
-  static_assert(K % KM == 0, "mode chunks tile the spectrum");
-  // staged offsets: all 7^3 (|d| <= 3), or for the central cubes the 5^3 with |d| <= 2
-  constexpr int OW = CENTRAL ? 5 : 7, OR = OW / 2, NOFF = OW * OW * OW;
-  __shared__ cplx<T> s_g[NOFF * KM];  // [offset][mode], offset (dx+OR) + OW (dy+OR) + OW^2 (dz+OR)
-  __shared__ int s_src[PP * 216];      // source spectrum rows of the group's blocks
-  const int tid = threadIdx.x, m = tid % KM, pp = tid / KM;
-  const int k0 = blockIdx.x * KM, k = k0 + m;
-  const cplx<T>* G = a.gcell + size_t(tlevel - 2) * S::OFFS * K + k0;
-  for (int e = tid; e < NOFF * KM; e += 256) {
-    const int o = e / KM;
-    const int dx = o % OW - OR, dy = (o / OW) % OW - OR, dz = o / (OW * OW) - OR;
-    const int o343 = (dx + 3) + 7 * (dy + 3) + 49 * (dz + 3);  // the table's layout
-    s_g[e] = G[size_t(o343) * K + e % KM];
-  }
-  // every group iteration runs in all threads of the workgroup (uniform trip count)
-  for (int grp = blockIdx.y; pbeg + grp * PP < pend; grp += gridDim.y) {
-    __syncthreads();  // the previous group's slot rows are consumed
-    for (int e = tid; e < PP * 216; e += 256) {
-      const int q = pbeg + grp * PP + e / 216;
-      int v = a.nsources;  // the zero row
-      if (q < pend) {
-        const int src = a.blocks[size_t(plist[q] - a.first_parent) * 216 + e % 216];
-        if (src >= 0) v = src - a.first_cell;
+  using A = AccumShape<CENTRAL>;
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  constexpr int KP = S::KP, KC = kChunkModes<double>, NCH = KP / KC;  // KP is a multiple of 16
+  constexpr int OW = A::OW, OR = A::OR, NOFF = A::NOFF, B0 = A::B0, NB = A::NB, NU = NB / 2;
+  constexpr int TILE = kTileParents<double, CENTRAL>, WP = 8;  // parents of a tile, of a wave
+  constexpr int PC = 8;                               // 16-byte pieces: 4 mode pairs x 2 parts
+  __shared__ d2 s_g[NOFF * PC];                       // [offset][pieces, swizzled]
+  __shared__ d2 s_b[TILE / WP][4 * WP * PC];          // per wave: [slot][parent][pieces, swizzled]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, q = lane >> 4;
+  // as operand A: row n = (child, part of G). Register r of the accumulator holds row 4 r + q: with
+  // the part in bit 2 of the row a lane gets both parts of children q and q + 4.
+  const int achild = (n & 3) | ((n >> 3) << 2), apart = (n >> 2) & 1;
+  const int cx = achild & 1, cy = (achild >> 1) & 1, cz = achild >> 2;
+  const int ox = (q & 1) + 1 - cx, oy = (q >> 1) + 1 - cy, oz = 1 - cz;  // offset of slot (0, 0, 0)
+  const int aswz = (ox & 1) * 2 + (oy & 1) * 4;
+  const d2* ga = s_g + (ox + OW * oy + OW * OW * oz) * PC;
+  // as operand B: column n = (parent, part of S)
+  const int bpar = n >> 1, bpart = n & 1;
+  const d2* sb = s_b[wave] + (q * WP + bpar) * PC;
+  const int bswz = (bpar >> 1) << 1;
+  // as a loader: piece lane % 8 of parent lane / 8, the 4 slots of the step in turn
+  const int lpar = lane >> 3, lpiece = lane & 7;
+  d2* sw = s_b[wave] + lpar * PC + (lpiece ^ ((lpar >> 1) << 1));
+
+  const Items items(NCH * tt.ntiles);
+  int staged = -1;
+  for (int it = items.begin; it < items.end; it += items.step) {
+    int chunk, lp, p0, pn;
+    item_of<TILE>(tt, it, chunk, lp, p0, pn);
+    if (staged != chunk * kMaxLevelsHost + lp) {  // workgroup-uniform
+      staged = chunk * kMaxLevelsHost + lp;
+      __syncthreads();  // the previous item's Green values are consumed
+      // the children's level is lp + 1
+      const double* G = a.gcell + size_t(lp - 1) * S::OFFS * 2 * KP + chunk * 2 * KC;
+      for (int e = tid; e < NOFF * PC; e += kAccumThreads<double, CENTRAL>) {
+        const int o = e / PC, j = e % PC;
+        const int x = o % OW, y = (o / OW) % OW, z = o / (OW * OW);
+        const int o343 = (x + 3 - OR) + 7 * (y + 3 - OR) + 49 * (z + 3 - OR);
+        s_g[o * PC + (j ^ ((x & 1) * 2 + (y & 1) * 4))] =
+            reinterpret_cast<const d2*>(G + size_t(o343) * 2 * KP)[j];
       }
-      s_src[e] = v;
+      __syncthreads();
     }
-    __syncthreads();
-    const int idx = pbeg + grp * PP + pp;
-    if (idx >= pend) continue;
-    const int par = plist[idx];
-    const int* row = s_src + pp * 216;
-    cplx<T> acc[8];
+    if (wave * WP >= pn) continue;  // wave-uniform; the barriers above are workgroup-uniform
+    // row ids of the loader's parent (the zero row for an empty slot; any valid table row for an
+    // absent parent, whose ids are not used): lane % 4 holds slot lane % 4 of a step
+    const bool have = wave * WP + lpar < pn;
+    const int* ids = a.blocks + size_t(plist[p0 + min(wave * WP + lpar, pn - 1)] - a.first_parent) * 216 +
+                     B0 * 43 + (lane & 1) + 6 * ((lane >> 1) & 1);
+    auto load_ids = [&](int u, int v, int bz) {
+      const int r = ids[2 * u + 12 * v + 36 * bz];
+      return have && r >= 0 ? r - a.first_cell : a.nsources;
+    };
+    const double* spec = a.sspec + chunk * 2 * KC + lpiece * 2;
+    d2 rows[4];
+    auto load_rows = [&](int idv, d2 (&to)[4]) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = {T(0), T(0)};
-    // two planes at a time in FP32, so that one plane's loads overlap the other's arithmetic
-    // (FP64 has no registers to spare for it)
-#pragma unroll sizeof(T) == 4 ? 2 : 1
-    for (int bz = CENTRAL ? 1 : 0; bz < (CENTRAL ? 5 : 6); ++bz) {
-      cplx<T> sp[36];
-#pragma unroll
-      for (int j = 0; j < 36; ++j) {
-        const int jx = j % 6, jy = j / 6;
-        if (CENTRAL && (jx < 1 || jx > 4 || jy < 1 || jy > 4)) continue;
-        sp[j] = a.sspec[size_t(row[bz * 36 + j]) * K + k];
+      for (int k = 0; k < 4; ++k) {
+        const int r = __shfl(idv, (lane & 60) + k, 64);
+        to[k] = *reinterpret_cast<const d2*>(spec + size_t(r) * 2 * KP);
       }
+    };
+    d4 acc[8];
 #pragma unroll
-      for (int cz = 0; cz < 2; ++cz) {
-        const int dz = bz - 2 - cz;  // in [-3, 3]; in [-2, 2] for the central planes
-        const bool zfar = dz < -1 || dz > 1;
-        const cplx<T>* gz = s_g + (OW * OW * (dz + OR)) * KM + m;
+    for (int m = 0; m < 8; ++m) acc[m] = d4{0.0, 0.0, 0.0, 0.0};
+    load_rows(load_ids(0, 0, 0), rows);
+    int id_next = load_ids(1, 0, 0);
+    for (int bz = 0; bz < NB; ++bz) {
 #pragma unroll
-        for (int dy = -3; dy <= 3; ++dy) {
+      for (int st = 0; st < NU * NU; ++st) {
+        const int u = st % NU, v = st / NU;
+        wave_lds_fence();
 #pragma unroll
-          for (int dx = -3; dx <= 3; ++dx) {
-            const bool far_xy = dx < -1 || dx > 1 || dy < -1 || dy > 1;
-            if (!far_xy && !zfar) continue;  // the 27 offsets of the near zone
-            if (CENTRAL && (dx < -2 || dx > 2 || dy < -2 || dy > 2)) continue;  // no central source
-            const cplx<T> gv = gz[((dx + OR) + OW * (dy + OR)) * KM];
+        for (int k = 0; k < 4; ++k) sw[k * WP * PC] = rows[k];
+        wave_lds_fence();
+        if (st + 1 < NU * NU || bz + 1 < NB) {
+          load_rows(id_next, rows);
+          constexpr int NN = NU * NU;
+          if (st + 2 < NN) id_next = load_ids((st + 2) % NU, (st + 2) / NU, bz);
+          else if (bz + 1 < NB) id_next = load_ids((st + 2 - NN) % NU, (st + 2 - NN) / NU, bz + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of this step's products
+        const d2* gs = ga + (2 * u + 2 * OW * v + OW * OW * bz) * PC;
 #pragma unroll
-            for (int cy = 0; cy < 2; ++cy) {
-#pragma unroll
-              for (int cx = 0; cx < 2; ++cx) {
-                const int by = dy + 2 + cy, bx = dx + 2 + cx;
-                if (by < 0 || by > 5 || bx < 0 || bx > 5) continue;
-                if (CENTRAL && (by < 1 || by > 4 || bx < 1 || bx > 4)) continue;
-                cplx<T>& o = acc[cx | (cy << 1) | (cz << 2)];
-                const cplx<T> sv = sp[by * 6 + bx];
-                o.re = fma(gv.re, sv.re, o.re);
-                o.re = fma(-gv.im, sv.im, o.re);
-                o.im = fma(gv.re, sv.im, o.im);
-                o.im = fma(gv.im, sv.re, o.im);
-              }
-            }
-          }
+        for (int w = 0; w < 4; ++w) {
+          const d2 g = gs[(2 * w + apart) ^ aswz], b = sb[(2 * w + bpart) ^ bswz];
+          acc[2 * w] = __builtin_amdgcn_mfma_f64_16x16x4f64(g.x, b.x, acc[2 * w], 0, 0, 0);
+          acc[2 * w + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(g.y, b.y, acc[2 * w + 1], 0, 0, 0);
         }
       }
     }
+    // D(c, Gr), D(c, Gi) of this column's part of S: the real part of T_c is D(Gr) of the real
+    // column minus D(Gi) of the imaginary one, the imaginary part the sum of the other two
+    const int k = wave * WP + bpar;
+    const int* kids = a.child8 + size_t(plist[p0 + min(k, pn - 1)]) * 8;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int t = a.child8[size_t(par) * 8 + c];
-      if (t >= 0) a.tspec[size_t(t - a.first_cell) * K + k] = acc[c];
+    for (int h = 0; h < 2; ++h) {
+      const int t = k < pn ? kids[q + 4 * h] : -1;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const double x0 = __shfl_xor(acc[2 * w][2 * h + 1], 1, 64);
+        const double x1 = __shfl_xor(acc[2 * w + 1][2 * h + 1], 1, 64);
+        const d2 o = bpart ? d2{acc[2 * w][2 * h] + x0, acc[2 * w + 1][2 * h] + x1}
+                           : d2{acc[2 * w][2 * h] - x0, acc[2 * w + 1][2 * h] - x1};
+        if (t >= 0)
+          *reinterpret_cast<d2*>(a.tspec + size_t(t - a.first_cell) * 2 * KP + chunk * 2 * KC +
+                                 (2 * w + bpart) * 2) = o;
+      }
     }
   }
 }
 
 // target node t (0 .. NL-1) of an axis sits at cyclic index t - EXT (mod C)
 template <int C, int EXT>
-__device__ __forceinline__ int cyc(int t) { return t >= EXT ? t - EXT : t - EXT + C; }
+__host__ __device__ constexpr int cyc(int t) { return t >= EXT ? t - EXT : t - EXT + C; }
+
+// out_t = sum_k f[k] exp(+2 pi i k t' / C) at the NL target nodes t (t' = cyc(t)), handed to
+// put(t, value); compile-time twiddles
+template <int NL, int C, int EXT, typename F>
+__device__ __forceinline__ void inverse_line(const cplx<double> (&f)[C], F&& put) {
+  static_for<0, NL>([&](auto tc) {
+    constexpr int t = cyc<C, EXT>(decltype(tc)::value);
+    cplx<double> acc = f[0];
+    static_for<1, C>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      constexpr double wr = cis_cos(long(k) * t, C), wi = cis_sin(long(k) * t, C);
+      acc.re = fma(f[k].re, wr, acc.re);
+      acc.re = fma(-f[k].im, wi, acc.re);
+      acc.im = fma(f[k].re, wi, acc.im);
+      acc.im = fma(f[k].im, wr, acc.im);
+    });
+    put(tc, acc);
+  });
+}
 
 // ADD: the target already holds (mean, zero-mean gridlet) from the transform shared by its
 // parent's children; this pass adds its own mean and zero-mean part to them (both precisions).
+//
+// Whole lines per thread, samples in registers and twiddles as immediates, instead of one output
+// per thread with samples and twiddles from LDS (whose reads bounded it): 2^24 clustered particles,
+// N_g = 4, FP32 2.88 -> 0.91 ms (4.5 GB read); 2^18 Plummer, N_g = 6 0.092 -> 0.035 ms.
 template <typename T, int NG, int EXT, bool ADD = false>
-__global__ __launch_bounds__(256) void k_cells_inverse(CellArgs<T> a) {
+__global__ __launch_bounds__(kCellThreads) void k_cells_inverse(CellArgs<T> a) {
   using S = CellShape<NG, EXT>;
-  constexpr int C = S::C, HC = S::HC, K = S::K, NL = S::NL, M = S::ML;
+  constexpr int C = S::C, HC = S::HC, KP = S::KP, NL = S::NL, M = S::ML;
   constexpr bool split = ADD || sizeof(T) == 4;
-  __shared__ cplx<double> tw[C];
-  __shared__ cplx<double> s_f[K];              // [kz][ky][kx]
-  __shared__ cplx<double> s_b1[NL * C * HC];   // [z][ky][kx], target z
-  __shared__ cplx<double> s_b2[NL * NL * HC];  // [z][y][kx]
-  __shared__ double s_out[M];
-  __shared__ double s_red[4];
-  const int t = blockIdx.x, tid = threadIdx.x;
-  load_twiddles<double, C>(tw, 1.0);
-  const cplx<T>* f = a.tspec + size_t(t) * S::KP;
-  for (int e = tid; e < K; e += 256) s_f[e] = {double(f[e].re), double(f[e].im)};
-  __syncthreads();
-  for (int e = tid; e < NL * C * HC; e += 256) {
-    const int col = e % (C * HC), zc = cyc<C, EXT>(e / (C * HC));
-    cplx<double> acc = {0.0, 0.0};
-    int m = 0;
+  constexpr int PER = cells_per_group<NG, EXT>();
+  __shared__ cplx<double> s_b1[PER * NL * C * HC];   // [target][z][ky][kx]
+  __shared__ cplx<double> s_b2[PER * NL * NL * HC];  // [target][z][y][kx]
+  __shared__ double s_row[split ? PER * NL * NL : 1];
+  const int tid = threadIdx.x;
+  const int t0 = blockIdx.x * PER;
+  const int cnt = min(PER, a.ntargets - t0);
+  // z: one column (target, ky, kx) per thread, the NL target z values
+  for (int q = tid; q < cnt * C * HC; q += kCellThreads) {
+    const int tl = q / (C * HC), col = q % (C * HC);
+    const T* row = a.tspec + size_t(t0 + tl) * 2 * KP;
+    cplx<double> f[C];
+    // C is even: whole mode pairs, 16 or 32 bytes, aligned
+    typedef T t4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int kz = 0; kz < C; ++kz) {
-      acc = cadd(acc, cmul(s_f[kz * C * HC + col], tw[m]));
-      m += zc;
-      if (m >= C) m -= C;
+    for (int j = 0; j < C / 2; ++j) {
+      const t4 v = *reinterpret_cast<const t4*>(row + 2 * (col * C + 2 * j));
+      f[2 * j] = {double(v[mode_pos<T>(0, 0)]), double(v[mode_pos<T>(0, 1)])};
+      f[2 * j + 1] = {double(v[mode_pos<T>(1, 0)]), double(v[mode_pos<T>(1, 1)])};
     }
-    s_b1[e] = acc;
+    inverse_line<NL, C, EXT>(f, [&](auto zc, cplx<double> o) {
+      s_b1[(tl * NL + decltype(zc)::value) * C * HC + col] = o;
+    });
   }
   __syncthreads();
-  for (int e = tid; e < NL * NL * HC; e += 256) {
-    const int kx = e % HC, yc = cyc<C, EXT>((e / HC) % NL), z = e / (HC * NL);
-    cplx<double> acc = {0.0, 0.0};
-    int m = 0;
+  // y: one column (target, z, kx) per thread, the NL target y values
+  for (int q = tid; q < cnt * NL * HC; q += kCellThreads) {
+    const int z = q / HC, kx = q % HC;  // z: (target, z)
+    cplx<double> f[C];
 #pragma unroll
-    for (int ky = 0; ky < C; ++ky) {
-      acc = cadd(acc, cmul(s_b1[(z * C + ky) * HC + kx], tw[m]));
-      m += yc;
-      if (m >= C) m -= C;
-    }
-    s_b2[e] = acc;
+    for (int ky = 0; ky < C; ++ky) f[ky] = s_b1[(z * C + ky) * HC + kx];
+    inverse_line<NL, C, EXT>(f, [&](auto yc, cplx<double> o) {
+      s_b2[(z * NL + decltype(yc)::value) * HC + kx] = o;
+    });
   }
   __syncthreads();
-  const int g = a.first_cell + t;
-  T* out = a.local + size_t(g) * M;
-  double part = 0.0;
-  for (int e = tid; e < M; e += 256) {
-    const int xc = cyc<C, EXT>(e % NL), zy = e / NL;  // zy = z * NL + y
-    // real part of the Hermitian sum over kx in (-C/2, C/2]: the kx = 0 and kx = C/2 (Nyquist)
-    // terms once, the others twice
-    double acc = 0.0;
-    int m = 0;
+  // x: one row (target, z, y) per thread, the real part of the Hermitian sum over kx in
+  // (-C/2, C/2]: the kx = 0 and kx = C/2 (Nyquist) terms once, the others twice
+  const int g0 = a.first_cell + t0;
+  constexpr int ROUNDS = (PER * NL * NL + kCellThreads - 1) / kCellThreads;
+  double out[ROUNDS][NL];
 #pragma unroll
-    for (int kx = 0; kx < HC; ++kx) {
-      const cplx<double> v = s_b2[zy * HC + kx];
-      const double re = v.re * tw[m].re - v.im * tw[m].im;
-      acc += (kx == 0 || kx == C / 2) ? re : 2.0 * re;
-      m += xc;
-      if (m >= C) m -= C;
-    }
-    if constexpr (split) {
-      s_out[e] = acc;
-      part += acc;
-    } else {
-      out[e] = T(acc);
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int e = tid + r * kCellThreads;  // (target, z, y)
+    if (e >= cnt * NL * NL) continue;
+    cplx<double> f[HC];
+#pragma unroll
+    for (int kx = 0; kx < HC; ++kx) f[kx] = s_b2[e * HC + kx];
+    double sum = 0.0;
+    static_for<0, NL>([&](auto xc) {
+      constexpr int X = cyc<C, EXT>(decltype(xc)::value);
+      double acc = f[0].re;
+      static_for<1, HC>([&](auto kc) {
+        constexpr int kx = decltype(kc)::value;
+        constexpr double w = kx == C / 2 ? 1.0 : 2.0;
+        constexpr double wr = w * cis_cos(long(kx) * X, C), wi = w * cis_sin(long(kx) * X, C);
+        acc = fma(f[kx].re, wr, acc);
+        acc = fma(-f[kx].im, wi, acc);
+      });
+      out[r][decltype(xc)::value] = acc;
+      sum += acc;
+    });
+    if constexpr (split) s_row[e] = sum;
+    else {
+#pragma unroll
+      for (int x = 0; x < NL; ++x) a.local[size_t(g0) * M + size_t(e) * NL + x] = T(out[r][x]);
     }
   }
   if constexpr (split) {
-    part = wave_sum(part);
-    if ((tid & 63) == 0) s_red[tid >> 6] = part;
     __syncthreads();
-    const double mean = (s_red[0] + s_red[1] + s_red[2] + s_red[3]) * (1.0 / M);
-    if constexpr (ADD) {
-      for (int e = tid; e < M; e += 256) out[e] = T(double(out[e]) + (s_out[e] - mean));
-      if (tid == 0) a.m2l_mean[g] += mean;
-    } else {
-      for (int e = tid; e < M; e += 256) out[e] = T(s_out[e] - mean);
-      if (tid == 0) a.m2l_mean[g] = mean;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int e = tid + r * kCellThreads;
+      if (e >= cnt * NL * NL) continue;
+      const int tl = e / (NL * NL);
+      double mean = 0.0;
+      for (int k = 0; k < NL * NL; ++k) mean += s_row[tl * NL * NL + k];
+      mean *= 1.0 / M;
+      T* o = a.local + size_t(g0) * M + size_t(e) * NL;
+#pragma unroll
+      for (int x = 0; x < NL; ++x) {
+        if constexpr (ADD) o[x] = T(double(o[x]) + (out[r][x] - mean));
+        else o[x] = T(out[r][x] - mean);
+      }
+      if (e % (NL * NL) == 0) {
+        if constexpr (ADD) a.m2l_mean[g0 + tl] += mean;
+        else a.m2l_mean[g0 + tl] = mean;
+      }
     }
   }
 }
@@ -372,35 +757,45 @@ static void cells_t(Plan& p, hipStream_t s) {
   const int ntargets = int(p.ncells) - a.first_cell;
   if (ntargets <= 0) return;
   a.nsources = ntargets + int(p.nvirt);
+  a.ntargets = ntargets;
   a.first_parent = p.blocks_first;
-  a.nlevels = p.nlevels;
-  a.level_off = p.dlev.as<int>() + kLevOff;
   a.child8 = p.child8.as<int>();
   a.blocks = p.blocks.as<int>();
   a.gridlet = p.gridlet.as<T>();
   a.local = p.local.as<T>();
-  a.gcell = p.tab.gcell.as<cplx<T>>();
-  a.sspec = p.cell_src.as<cplx<T>>();
-  a.tspec = p.cell_tgt.as<cplx<T>>();
+  a.gcell = p.tab.gcell.as<T>();
+  a.sspec = p.cell_src.as<T>();
+  a.tspec = p.cell_tgt.as<T>();
   a.m2l_mean = p.m2l_mean.as<double>();
   if (p.tab.gcell_levels < p.nlevels - 2) fail(HPM_ERR_DEVICE, "cell Green tables missing");
   if (p.cell_src.bytes < size_t(a.nsources + 1) * S::KP * sizeof(cplx<T>) ||
       p.cell_tgt.bytes < size_t(ntargets) * S::KP * sizeof(cplx<T>) ||
       p.local.bytes < size_t(p.ncells) * S::ML * sizeof(T))
     fail(HPM_ERR_DEVICE, "cell spectra buffers too small");
-  k_cells_forward<T, NG, EXT><<<(a.nsources + kFwdSources) / kFwdSources, kFwdThreads, 0, s>>>(a);
+  constexpr int PER = cells_per_group<NG, EXT>();
+  k_cells_forward<T, NG, EXT><<<a.nsources / PER + 1, kCellThreads, 0, s>>>(a);
   HPM_LAUNCH_CHECK();
-  using A = AccumShape<T>;
-  for (int lp = 1; lp + 1 < p.nlevels; ++lp) {
-    const int pbeg = p.cell_pbeg[lp], pend = p.cell_pbeg[lp + 1];
-    if (pend <= pbeg) continue;
-    const int groups = std::min((pend - pbeg + A::PP - 1) / A::PP, 65535);
-    k_cells_accum<T, NG, EXT, SHARED><<<dim3(S::KP / A::KM, groups), 256, 0, s>>>(
-        a, lp + 1, p.cell_plist.as<int>(), pbeg, pend);
+  TileTable tt{};
+  constexpr int TILE = kTileParents<T, SHARED>;
+  for (int lp = 1; lp <= kMaxLevelsHost; ++lp) {
+    tt.first[lp] = tt.ntiles;
+    tt.pbeg[lp] = p.cell_pbeg[std::min(lp, p.nlevels - 1)];
+    if (lp + 1 < p.nlevels)
+      tt.ntiles += (p.cell_pbeg[lp + 1] - p.cell_pbeg[lp] + TILE - 1) / TILE;
+  }
+  if (tt.ntiles > 0) {
+    constexpr int64_t chunks = (S::KP + kChunkModes<T> - 1) / kChunkModes<T>;
+    const int64_t items = chunks * tt.ntiles;
+    if (items > (int64_t(1) << 30)) fail(HPM_ERR_UNSUPPORTED, "too many cells for the cell-by-cell route");
+    const int grid = int(std::min<int64_t>((items + 7) / 8 * 8, 256 * kAccumPerCU<T, SHARED>));
+    if constexpr (sizeof(T) == 4)
+      k_cells_accum_f32<NG, EXT, SHARED><<<grid, kAccumThreads<T, SHARED>, 0, s>>>(a, tt, p.cell_plist.as<int>());
+    else
+      k_cells_accum_f64<NG, EXT, SHARED><<<grid, kAccumThreads<T, SHARED>, 0, s>>>(a, tt, p.cell_plist.as<int>());
     HPM_LAUNCH_CHECK();
   }
   if constexpr (SHARED) launch_m2l_parents(p, s);
-  k_cells_inverse<T, NG, EXT, SHARED><<<ntargets, 256, 0, s>>>(a);
+  k_cells_inverse<T, NG, EXT, SHARED><<<(ntargets + PER - 1) / PER, kCellThreads, 0, s>>>(a);
   HPM_LAUNCH_CHECK();
 }
 

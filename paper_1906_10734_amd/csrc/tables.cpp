@@ -149,7 +149,7 @@ static std::vector<double> cell_green(const Plan& p, int nlev) {
             a2r[(size_t(z) * C + ky) * HC + kx] = re;
             a2i[(size_t(z) * C + ky) * HC + kx] = im;
           }
-      // z: [kz][ky][kx], interleaved (re, im), / C^3
+      // z, / C^3
       double* o = &out[(size_t(li) * 343 + od) * Kp * 2];
       for (int kz = 0; kz < C; ++kz)
         for (int col = 0; col < C * HC; ++col) {
@@ -160,8 +160,11 @@ static std::vector<double> cell_green(const Plan& p, int nlev) {
             re += a2r[i] * c - a2i[i] * sv;
             im += a2r[i] * sv + a2i[i] * c;
           }
-          o[(size_t(kz) * C * HC + col) * 2] = re * inv;
-          o[(size_t(kz) * C * HC + col) * 2 + 1] = im * inv;
+          // stored order: kz fastest; (re, im) interleaved, or in FP64 two real parts, then two
+          // imaginary ones
+          const int k = col * C + kz, gm = p.elem == 4 ? 1 : 2, at = (k / gm) * 2 * gm + k % gm;
+          o[at] = re * inv;
+          o[at + gm] = im * inv;
         }
     }
   }
