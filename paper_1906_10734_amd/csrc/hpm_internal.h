@@ -142,11 +142,12 @@ struct Tables {
   DevBuf l2l;    // [2][NL][NL]: the same on the target gridlet's nodes (equal to m2m unless
                  // the gridlets are extended)
   DevBuf fitw;   // [Kpad][Mpad]: W[n][p] = B^phi[p][n], Legendre-moment fit matrix, zero padded
-  DevBuf ghat;   // [levels 2..L][(n/2+1)^3]: octant of the lattice Green transform / n^3
+  DevBuf ghat;   // N_g <= 3: [levels 2..L][(n/2+1)^3]: octant of the lattice Green transform / n^3
   DevBuf gxy;    // [levels 2..L][4 N_g + 1][n/2+1][n/2+1]: Green function transformed along x
                  // and y only, at z offsets d <= 4 N_g, [d][ky][kx], / n^2
-  DevBuf gcell;  // cell-by-cell and shared-transform routes only: [levels 2..L][343 offsets][(2N_g)^2 (N_g+1)] complex,
-                 // transform of the cyclic Green array of each source cube offset, / (2 N_g)^3
+  DevBuf gcell;  // cell-by-cell and shared-transform routes only: [levels 2..L][343 offsets][modes],
+                 // transform of the cyclic Green array of each source cube offset, / C^3, in the
+                 // stored order of the cell spectra
   DevBuf twff;   // FP32 plans: [8 N_g] e^{+2 pi i m / n} as {cos hi, sin hi, cos lo, sin lo}
   int kpad = 0, mpad = 0;
   int ghat_levels = 0;

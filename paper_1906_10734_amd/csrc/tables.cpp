@@ -1,5 +1,10 @@
-// Constant tables, built on the host in double precision and rounded once to the plan's dtype
-// (the paper precomputes the Green function and the matrices A, B, T before timing, Sec. 4).
+// Constant tables, in double precision and rounded once to the plan's dtype (the paper precomputes
+// the Green function and the matrices A, B, T before timing, Sec. 4). The host computes what is one
+// dimensional (cosines, the 1-D fit and interpolation matrices, at most 4 KB) and passes it to the
+// kernels below by value; they form the tables in place. A plan's creation pays for them: on the
+// host they took 2.3 of the 3.5 ms of a one-shot solve of 3000 particles at N_g = 4, and 0.1 s of a
+// plan with cell spectra at N_g = 6; here they are four launches with no copy and no wait. Sums run
+// in index order without contraction, as they did there, so the values are the same.
 //
 //   fit matrix   Effective masses from moments (Sec. 2.2, Eq. 4-5). The moments here are taken
 //                in the tensor Legendre basis phi_n(x) = P_nx(2x) P_ny(2y) P_nz(2z), which spans
@@ -31,6 +36,7 @@
 //                row padded with zeros to a multiple of 16 modes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -89,232 +95,315 @@ static std::vector<double> invert(std::vector<double> a, int n) {
   return inv;
 }
 
-// Transforms of the cyclic Green arrays of the cell-by-cell route, all levels and offsets.
-static std::vector<double> cell_green(const Plan& p, int nlev) {
-  const int ng = p.ng, ext = p.ext, C = 2 * ng + 2 * ext, HC = C / 2 + 1;
-  const int Kp = int(cell_modes(ng, ext));  // C^2 HC modes, padded
-  std::vector<double> out(size_t(std::max(nlev, 1)) * 343 * Kp * 2, 0.0);
-  std::vector<double> cs(size_t(C) * C), sn(size_t(C) * C);
-  for (int k = 0; k < C; ++k)
-    for (int j = 0; j < C; ++j) {
-      const double ang = 2.0 * M_PI * double((k * j) % C) / double(C);
-      cs[size_t(k) * C + j] = std::cos(ang);
-      sn[size_t(k) * C + j] = -std::sin(ang);
-    }
-  const double G = p.prob.gconst, eps = p.prob.softening, inv = 1.0 / (double(C) * C * C);
-  std::vector<double> g(size_t(C) * C * C);
-  std::vector<double> a1r(size_t(C) * C * HC), a1i(a1r.size()), a2r(size_t(C) * C * HC),
-      a2i(a2r.size());
-  for (int li = 0; li < nlev; ++li) {
-    const double h = p.prob.box_size / (double(1 << (li + 2)) * ng);
-    for (int od = 0; od < 343; ++od) {
-      const int d[3] = {od % 7 - 3, (od / 7) % 7 - 3, od / 49 - 3};
-      if (std::abs(d[0]) <= 1 && std::abs(d[1]) <= 1 && std::abs(d[2]) <= 1) continue;  // near
-      for (int z = 0; z < C; ++z)
-        for (int y = 0; y < C; ++y)
-          for (int x = 0; x < C; ++x) {
-            const int u[3] = {x, y, z};
-            double r2 = 0.0;
-            for (int a = 0; a < 3; ++a) {
-              const double o = double(d[a] * ng - (u[a] < ng + ext ? u[a] : u[a] - C));
-              r2 += o * o;
-            }
-            const double sd = std::sqrt(r2 * h * h + eps * eps);
-            g[(size_t(z) * C + y) * C + x] = (p.prob.kernel == HPM_KERNEL_YUKAWA)
-                                                 ? -G * std::exp(-sd / p.prob.screening) / sd
-                                                 : -G / sd;
-          }
-      // x (real input): a1[z][y][kx]
-      for (int zy = 0; zy < C * C; ++zy)
-        for (int kx = 0; kx < HC; ++kx) {
-          double re = 0.0, im = 0.0;
-          for (int x = 0; x < C; ++x) {
-            re += g[size_t(zy) * C + x] * cs[size_t(kx) * C + x];
-            im += g[size_t(zy) * C + x] * sn[size_t(kx) * C + x];
-          }
-          a1r[size_t(zy) * HC + kx] = re;
-          a1i[size_t(zy) * HC + kx] = im;
-        }
-      // y: a2[z][ky][kx]
-      for (int z = 0; z < C; ++z)
-        for (int ky = 0; ky < C; ++ky)
-          for (int kx = 0; kx < HC; ++kx) {
-            double re = 0.0, im = 0.0;
-            for (int y = 0; y < C; ++y) {
-              const size_t i = (size_t(z) * C + y) * HC + kx;
-              const double c = cs[size_t(ky) * C + y], sv = sn[size_t(ky) * C + y];
-              re += a1r[i] * c - a1i[i] * sv;
-              im += a1r[i] * sv + a1i[i] * c;
-            }
-            a2r[(size_t(z) * C + ky) * HC + kx] = re;
-            a2i[(size_t(z) * C + ky) * HC + kx] = im;
-          }
-      // z, / C^3
-      double* o = &out[(size_t(li) * 343 + od) * Kp * 2];
-      for (int kz = 0; kz < C; ++kz)
-        for (int col = 0; col < C * HC; ++col) {
-          double re = 0.0, im = 0.0;
-          for (int z = 0; z < C; ++z) {
-            const size_t i = size_t(z) * C * HC + col;
-            const double c = cs[size_t(kz) * C + z], sv = sn[size_t(kz) * C + z];
-            re += a2r[i] * c - a2i[i] * sv;
-            im += a2r[i] * sv + a2i[i] * c;
-          }
-          // stored order: kz fastest; (re, im) interleaved, or in FP64 two real parts, then two
-          // imaginary ones
-          const int k = col * C + kz, gm = p.elem == 4 ? 1 : 2, at = (k / gm) * 2 * gm + k % gm;
-          o[at] = re * inv;
-          o[at + gm] = im * inv;
-        }
-    }
+// ---- kernels ------------------------------------------------------------------------------------
+struct GreenKernel {
+  double gconst, eps, screening, box;
+  int yukawa;
+  // the kernel at lattice distance h sqrt(q)
+  __device__ double at(double h, double q) const {
+#pragma clang fp contract(off)
+    const double sd = sqrt(q * h * h + eps * eps);
+    return yukawa ? -gconst * exp(-sd / screening) / sd : -gconst / sd;
   }
-  return out;
+};
+
+struct Cosines {  // cos and sin of 2 pi m / n, m < n
+  double c[64];
+};
+struct CellTrig {  // cos and sin of 2 pi m / C
+  double c[16], s[16];
+};
+
+constexpr int kTableThreads = 256;
+
+// one plane z of the x-y transformed Green function of one level (grid: planes, levels), z, ky and
+// kx <= n/2: LDS holds the plane's kernel values, then its x transform
+__device__ __forceinline__ void green_plane(const GreenKernel& g, const double* s_cos, double* s_g,
+                                            double* s_a, int ng, int ext, int li, int z) {
+#pragma clang fp contract(off)
+  const int n = 8 * ng, H = n / 2 + 1;
+  const double h = g.box / (double(1 << (li + 2)) * ng);
+  for (int e = threadIdx.x; e < H * H; e += kTableThreads) {
+    const int x = e % H, y = e / H;
+    // Offsets with max-norm <= N_g join a target node only to nodes of the 27 cubes around the
+    // target, which are not sources; every interaction-zone pair is at least N_g + 1 apart along
+    // some axis (N_g with the extended target gridlet, whose outer nodes lie one spacing closer to
+    // the sources). Their values never reach a target potential, and zero keeps the largest
+    // (near-origin) kernel values out of the transform, where they would only add rounding error.
+    const bool unreachable = max(x, max(y, z)) <= ng - ext;
+    double v = 0.0;
+    if (!unreachable) {
+      const double r2 = h * h * double(x * x + y * y + z * z);
+      const double sd = sqrt(r2 + g.eps * g.eps);
+      v = g.yukawa ? -g.gconst * exp(-sd / g.screening) / sd : -g.gconst / sd;
+    }
+    s_g[e] = v;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < H * H; e += kTableThreads) {  // [y][kx]
+    const int kx = e % H, y = e / H;
+    double acc = 0.0;
+    for (int x = 0, m = 0; x < n; ++x) {
+      acc += s_g[y * H + (x <= n / 2 ? x : n - x)] * s_cos[m];
+      m += kx;
+      if (m >= n) m -= n;
+    }
+    s_a[e] = acc;
+  }
+  __syncthreads();
+}
+
+// sum over y of the x transform: entry (ky, kx) of the plane
+__device__ __forceinline__ double green_entry(const double* s_cos, const double* s_a, int n, int ky,
+                                              int kx) {
+#pragma clang fp contract(off)
+  const int H = n / 2 + 1;
+  double acc = 0.0;
+  for (int y = 0, m = 0; y < n; ++y) {
+    acc += s_a[(y <= n / 2 ? y : n - y) * H + kx] * s_cos[m];
+    m += ky;
+    if (m >= n) m -= n;
+  }
+  return acc;
+}
+
+constexpr int kMaxH = 33;  // N_g = 8
+
+template <typename T>
+__global__ __launch_bounds__(kTableThreads) void k_green_xy(GreenKernel g, Cosines cs, int ng, int ext,
+                                                            T* gxy) {
+#pragma clang fp contract(off)
+  __shared__ double s_cos[64], s_g[kMaxH * kMaxH], s_a[kMaxH * kMaxH];
+  const int n = 8 * ng, H = n / 2 + 1, z = blockIdx.x, li = blockIdx.y;
+  if (threadIdx.x < 64) s_cos[threadIdx.x] = cs.c[threadIdx.x];
+  green_plane(g, s_cos, s_g, s_a, ng, ext, li, z);
+  const double inv_n2 = 1.0 / (double(n) * n);
+  T* out = gxy + (size_t(li) * H + z) * H * H;  // planes d = z <= 4 N_g = n/2
+  for (int e = threadIdx.x; e < H * H; e += kTableThreads)
+    out[e] = T(green_entry(s_cos, s_a, n, e / H, e % H) * inv_n2);
+}
+
+// the full transform (N_g <= 3, the whole-grid kernel's table), one workgroup per level
+constexpr int kMaxSmallH = 13;
+template <typename T>
+__global__ __launch_bounds__(kTableThreads) void k_green_xyz(GreenKernel g, Cosines cs, int ng, int ext,
+                                                             T* ghat) {
+#pragma clang fp contract(off)
+  __shared__ double s_cos[64], s_g[kMaxSmallH * kMaxSmallH], s_a[kMaxSmallH * kMaxSmallH];
+  __shared__ double s_p[kMaxSmallH * kMaxSmallH * kMaxSmallH];
+  const int n = 8 * ng, H = n / 2 + 1, li = blockIdx.x;
+  if (threadIdx.x < 64) s_cos[threadIdx.x] = cs.c[threadIdx.x];
+  for (int z = 0; z < H; ++z) {
+    green_plane(g, s_cos, s_g, s_a, ng, ext, li, z);
+    for (int e = threadIdx.x; e < H * H; e += kTableThreads)
+      s_p[z * H * H + e] = green_entry(s_cos, s_a, n, e / H, e % H);
+    __syncthreads();
+  }
+  const double inv_n3 = 1.0 / (double(n) * n * n);
+  for (int e = threadIdx.x; e < H * H * H; e += kTableThreads) {
+    const int kz = e / (H * H), col = e % (H * H);
+    double acc = 0.0;
+    for (int z = 0, m = 0; z < n; ++z) {
+      acc += s_p[(z <= n / 2 ? z : n - z) * H * H + col] * s_cos[m];
+      m += kz;
+      if (m >= n) m -= n;
+    }
+    ghat[size_t(li) * H * H * H + e] = T(acc * inv_n3);
+  }
+}
+
+// Transform of the cyclic Green array of one source cube offset and level (grid: offsets, levels),
+// C <= 14: the kernel values and the y pass share one part of LDS, the x pass has the other.
+constexpr int kMaxC = 14, kMaxHC = 8;
+template <typename T>
+__global__ __launch_bounds__(kTableThreads) void k_green_cell(GreenKernel g, CellTrig tg, int ng, int ext,
+                                                              int KP, T* gcell) {
+#pragma clang fp contract(off)
+  __shared__ double s_c[16], s_s[16];
+  __shared__ double s_gv[2 * kMaxC * kMaxC * kMaxHC], s_a[2 * kMaxC * kMaxC * kMaxHC];
+  const int C = 2 * ng + 2 * ext, HC = C / 2 + 1, tid = threadIdx.x;
+  const int od = blockIdx.x, li = blockIdx.y;
+  const int d0 = od % 7 - 3, d1 = (od / 7) % 7 - 3, d2 = od / 49 - 3;
+  T* out = gcell + (size_t(li) * 343 + od) * KP * 2;
+  const bool near = abs(d0) <= 1 && abs(d1) <= 1 && abs(d2) <= 1;  // never used: zero
+  const int K = C * C * HC;
+  for (int e = near ? tid : 2 * K + tid; e < 2 * KP; e += kTableThreads) out[e] = T(0);
+  if (near) return;
+  if (tid < 16) {
+    s_c[tid] = tg.c[tid];
+    s_s[tid] = tg.s[tid];
+  }
+  const double h = g.box / (double(1 << (li + 2)) * ng);
+  for (int e = tid; e < C * C * C; e += kTableThreads) {
+    const int x = e % C, y = (e / C) % C, z = e / (C * C);
+    const double o0 = double(d0 * ng - (x < ng + ext ? x : x - C));
+    const double o1 = double(d1 * ng - (y < ng + ext ? y : y - C));
+    const double o2 = double(d2 * ng - (z < ng + ext ? z : z - C));
+    s_gv[e] = g.at(h, o0 * o0 + o1 * o1 + o2 * o2);
+  }
+  __syncthreads();
+  // x (real input): [z][y][kx]
+  for (int e = tid; e < K; e += kTableThreads) {
+    const int kx = e % HC, zy = e / HC;
+    double re = 0.0, im = 0.0;
+    for (int x = 0, m = 0; x < C; ++x) {
+      const double v = s_gv[zy * C + x];
+      re += v * s_c[m];
+      im += v * -s_s[m];
+      m += kx;
+      if (m >= C) m -= C;
+    }
+    s_a[2 * e] = re;
+    s_a[2 * e + 1] = im;
+  }
+  __syncthreads();
+  // y: [z][ky][kx]
+  for (int e = tid; e < K; e += kTableThreads) {
+    const int kx = e % HC, ky = (e / HC) % C, z = e / (HC * C);
+    double re = 0.0, im = 0.0;
+    for (int y = 0, m = 0; y < C; ++y) {
+      const int i = (z * C + y) * HC + kx;
+      const double ar = s_a[2 * i], ai = s_a[2 * i + 1], c = s_c[m], sv = -s_s[m];
+      re += ar * c - ai * sv;
+      im += ar * sv + ai * c;
+      m += ky;
+      if (m >= C) m -= C;
+    }
+    s_gv[2 * e] = re;
+    s_gv[2 * e + 1] = im;
+  }
+  __syncthreads();
+  // z, / C^3, into the stored order: kz fastest; (re, im) interleaved, or in FP64 two real parts,
+  // then two imaginary ones
+  const double inv = 1.0 / (double(C) * C * C);
+  constexpr int gm = sizeof(T) == 4 ? 1 : 2;
+  for (int e = tid; e < K; e += kTableThreads) {
+    const int kz = e % C, col = e / C;
+    double re = 0.0, im = 0.0;
+    for (int z = 0, m = 0; z < C; ++z) {
+      const int i = z * C * HC + col;
+      const double ar = s_gv[2 * i], ai = s_gv[2 * i + 1], c = s_c[m], sv = -s_s[m];
+      re += ar * c - ai * sv;
+      im += ar * sv + ai * c;
+      m += kz;
+      if (m >= C) m -= C;
+    }
+    const int at = (e / gm) * 2 * gm + e % gm;
+    out[at] = T(re * inv);
+    out[at + gm] = T(im * inv);
+  }
+}
+
+// the 1-D matrices, and what is formed from them
+struct Small {
+  double b1[64];    // 1-D fit matrix [p][k]
+  double t1[128];   // child-to-parent factors [2][N_g][N_g]
+  double t1l[128];  // the same on the target gridlet's nodes [2][NL][NL]
+  float tw[256];    // [8 N_g] {cos hi, sin hi, cos lo, sin lo}
+};
+
+template <typename T>
+__global__ __launch_bounds__(kTableThreads) void k_small_tables(Small s, int ng, int nl, int kpad,
+                                                                int mpad, T* fitw, T* m2m, T* l2l,
+                                                                float* twff) {
+#pragma clang fp contract(off)
+  const int M = ng * ng * ng;
+  const int e = blockIdx.x * kTableThreads + threadIdx.x;
+  if (e < kpad * mpad) {
+    const int n = e / mpad, q = e % mpad;
+    double w = 0.0;
+    if (n < M && q < M) {
+      const int nx = n % ng, ny = (n / ng) % ng, nz = n / (ng * ng);
+      const int px = q % ng, py = (q / ng) % ng, pz = q / (ng * ng);
+      w = s.b1[px * ng + nx] * s.b1[py * ng + ny] * s.b1[pz * ng + nz];
+    }
+    fitw[e] = T(w);
+  }
+  if (e < 2 * ng * ng) m2m[e] = T(s.t1[e]);
+  if (e < 2 * nl * nl) l2l[e] = T(s.t1l[e]);
+  if (twff && e < 32 * ng) twff[e] = s.tw[e];
 }
 
 template <typename T>
-static void upload(DevBuf& buf, const std::vector<double>& v, hipStream_t s) {
-  std::vector<T> h(v.begin(), v.end());
-  buf.reserve(h.size() * sizeof(T));
-  HPM_HIP(hipMemcpyAsync(buf.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-  HPM_HIP(hipStreamSynchronize(s));
+static void tables_t(Plan& p, int nlev, const Small& small, const Cosines& cs, const CellTrig& tg,
+                     hipStream_t s) {
+  const int ng = p.ng, n = 8 * ng, H = n / 2 + 1, kpad = p.tab.kpad, mpad = p.tab.mpad;
+  const GreenKernel g{p.prob.gconst, p.prob.softening, p.prob.screening, p.prob.box_size,
+                      p.prob.kernel == HPM_KERNEL_YUKAWA ? 1 : 0};
+  Tables& t = p.tab;
+  t.fitw.reserve(size_t(kpad) * mpad * sizeof(T));
+  t.m2m.reserve(size_t(2) * ng * ng * sizeof(T));
+  t.l2l.reserve(size_t(2) * p.NL * p.NL * sizeof(T));
+  if (sizeof(T) == 4) t.twff.reserve(size_t(n) * 16);
+  k_small_tables<T><<<(kpad * mpad + kTableThreads - 1) / kTableThreads, kTableThreads, 0, s>>>(
+      small, ng, p.NL, kpad, mpad, t.fitw.as<T>(), t.m2m.as<T>(), t.l2l.as<T>(),
+      sizeof(T) == 4 ? t.twff.as<float>() : nullptr);
+  HPM_LAUNCH_CHECK();
+  t.gxy.reserve(size_t(std::max(nlev, 1)) * H * H * H * sizeof(T));
+  if (nlev > 0) {
+    k_green_xy<T><<<dim3(H, nlev), kTableThreads, 0, s>>>(g, cs, ng, p.ext, t.gxy.as<T>());
+    HPM_LAUNCH_CHECK();
+  }
+  if (ng < 4) {
+    t.ghat.reserve(size_t(std::max(nlev, 1)) * H * H * H * sizeof(T));
+    if (nlev > 0) {
+      k_green_xyz<T><<<nlev, kTableThreads, 0, s>>>(g, cs, ng, p.ext, t.ghat.as<T>());
+      HPM_LAUNCH_CHECK();
+    }
+  }
+  if (p.prob.m2l_mode != HPM_M2L_GRID) {
+    const int KP = int(cell_modes(ng, p.ext));
+    t.gcell.reserve(size_t(std::max(nlev, 1)) * 343 * KP * 2 * sizeof(T));
+    if (nlev > 0) {
+      k_green_cell<T><<<dim3(343, nlev), kTableThreads, 0, s>>>(g, tg, ng, p.ext, KP, t.gcell.as<T>());
+      HPM_LAUNCH_CHECK();
+    }
+    t.gcell_levels = nlev;
+  }
 }
 
 void build_tables(Plan& p, int max_levels, hipStream_t s) {
-  const int ng = p.ng, M = ng * ng * ng;
+  const int ng = p.ng, M = ng * ng * ng, nl = p.NL, n = 8 * ng;
+  p.tab.kpad = (M + 3) / 4 * 4;
+  p.tab.mpad = (M + 15) / 16 * 16;
+  Small small{};
   // 1-D Legendre-at-nodes matrix and its inverse
   std::vector<double> pm(size_t(ng) * ng);
   for (int k = 0; k < ng; ++k)
     for (int q = 0; q < ng; ++q) pm[size_t(k) * ng + q] = legendre(k, 2.0 * node(ng, q));
   const std::vector<double> b1 = invert(pm, ng);  // b1[p][k]
-  const int kpad = (M + 3) / 4 * 4, mpad = (M + 15) / 16 * 16;
-  std::vector<double> w(size_t(kpad) * mpad, 0.0);
-  for (int nz = 0; nz < ng; ++nz)
-    for (int ny = 0; ny < ng; ++ny)
-      for (int nx = 0; nx < ng; ++nx)
-        for (int pz = 0; pz < ng; ++pz)
-          for (int py = 0; py < ng; ++py)
-            for (int px = 0; px < ng; ++px) {
-              const int n = nx + ng * (ny + ng * nz), q = px + ng * (py + ng * pz);
-              w[size_t(n) * mpad + q] = b1[size_t(px) * ng + nx] * b1[size_t(py) * ng + ny] *
-                                        b1[size_t(pz) * ng + nz];
-            }
-  p.tab.kpad = kpad;
-  p.tab.mpad = mpad;
-
-  std::vector<double> t1(size_t(2) * ng * ng);
+  std::copy(b1.begin(), b1.end(), small.b1);
   for (int a = 0; a < 2; ++a)
     for (int pp = 0; pp < ng; ++pp)
       for (int q = 0; q < ng; ++q)
-        t1[(size_t(a) * ng + pp) * ng + q] = lagrange(ng, pp, ((a ? 0.5 : -0.5) + node(ng, q)) / 2.0);
-  const int nl = p.NL;
-  std::vector<double> t1l(size_t(2) * nl * nl);
+        small.t1[(a * ng + pp) * ng + q] = lagrange(ng, pp, ((a ? 0.5 : -0.5) + node(ng, q)) / 2.0);
   for (int a = 0; a < 2; ++a)
     for (int pp = 0; pp < nl; ++pp)
       for (int q = 0; q < nl; ++q)
-        t1l[(size_t(a) * nl + pp) * nl + q] =
+        small.t1l[(a * nl + pp) * nl + q] =
             lagrange(ng, pp, ((a ? 0.5 : -0.5) + node(ng, q, p.ext)) / 2.0, p.ext);
-
-  // Green transforms, levels 2 .. nlevels-1
-  const int n = 8 * ng, H = n / 2 + 1;
+  // e^{+2 pi i m / n} as float pairs (hi, lo) per component, for the all-FP32 inverse transform
+  Cosines cs{};
+  for (int m = 0; m < n; ++m) {
+    const double c = std::cos(2.0 * M_PI * m / n), sn = std::sin(2.0 * M_PI * m / n);
+    const float ch = float(c), sh = float(sn);
+    small.tw[4 * m] = ch;
+    small.tw[4 * m + 1] = sh;
+    small.tw[4 * m + 2] = float(c - double(ch));
+    small.tw[4 * m + 3] = float(sn - double(sh));
+    cs.c[m] = c;
+  }
+  const int C = 2 * ng + 2 * p.ext;
+  CellTrig tg{};
+  for (int m = 0; m < C && m < 16; ++m) {
+    tg.c[m] = std::cos(2.0 * M_PI * double(m) / double(C));
+    tg.s[m] = std::sin(2.0 * M_PI * double(m) / double(C));
+  }
+  // Green transforms of levels 2 .. nlevels-1
   const int nlev = std::max(0, max_levels - 2);
-  std::vector<double> ghat(size_t(std::max(nlev, 1)) * H * H * H, 0.0);
-  const int D = 4 * ng + 1;
-  std::vector<double> gxy(size_t(std::max(nlev, 1)) * D * H * H, 0.0);
-  std::vector<double> cs(size_t(H) * n);
-  for (int k = 0; k < H; ++k)
-    for (int d = 0; d < n; ++d)
-      cs[size_t(k) * n + d] = std::cos(2.0 * M_PI * double((long(k) * d) % n) / double(n));
-  std::vector<int> pd(n);
-  for (int i = 0; i < n; ++i) pd[i] = (i <= n / 2) ? i : n - i;
-  const double G = p.prob.gconst, eps = p.prob.softening;
-  std::vector<double> g(size_t(n) * n * n), a1(size_t(n) * n * H), a2(size_t(n) * H * H);
-  for (int li = 0; li < nlev; ++li) {
-    const int l = li + 2;
-    const double h = p.prob.box_size / (double(1 << l) * ng);
-    for (int z = 0; z < n; ++z)
-      for (int y = 0; y < n; ++y)
-        for (int x = 0; x < n; ++x) {
-          double r2 = h * h * double(pd[x] * pd[x] + pd[y] * pd[y] + pd[z] * pd[z]);
-          if (x == 0 && y == 0 && z == 0 && eps == 0.0) r2 = h * h;
-          // Offsets with max-norm <= N_g join a target node only to nodes of the 27 cubes
-          // around the target, which are not sources; every interaction-zone pair is at least
-          // N_g + 1 apart along some axis (N_g with the extended target gridlet, whose outer
-          // nodes lie one spacing closer to the sources). Their values never reach a target
-          // potential, and zero keeps the largest (near-origin) kernel values out of the
-          // transform, where they would only add rounding error.
-          const bool unreachable = std::max(pd[x], std::max(pd[y], pd[z])) <= ng - p.ext;
-          double gv = 0.0;
-          if (!unreachable) {
-            const double sd = std::sqrt(r2 + eps * eps);
-            gv = (p.prob.kernel == HPM_KERNEL_YUKAWA) ? -G * std::exp(-sd / p.prob.screening) / sd
-                                                      : -G / sd;
-          }
-          g[(size_t(z) * n + y) * n + x] = gv;
-        }
-    // x: a1[z][y][kx]
-    for (int z = 0; z < n; ++z)
-      for (int y = 0; y < n; ++y)
-        for (int kx = 0; kx < H; ++kx) {
-          double acc = 0.0;
-          const double* row = &g[(size_t(z) * n + y) * n];
-          for (int x = 0; x < n; ++x) acc += row[x] * cs[size_t(kx) * n + x];
-          a1[(size_t(z) * n + y) * H + kx] = acc;
-        }
-    // y: a2[z][ky][kx]
-    for (int z = 0; z < n; ++z)
-      for (int ky = 0; ky < H; ++ky)
-        for (int kx = 0; kx < H; ++kx) {
-          double acc = 0.0;
-          for (int y = 0; y < n; ++y) acc += a1[(size_t(z) * n + y) * H + kx] * cs[size_t(ky) * n + y];
-          a2[(size_t(z) * H + ky) * H + kx] = acc;
-        }
-    // x, y only: gxy[d][ky][kx] = a2[d][ky][kx] / n^2, d <= 4 N_g
-    const double inv_n2 = 1.0 / (double(n) * n);
-    for (size_t e = 0; e < size_t(D) * H * H; ++e) gxy[size_t(li) * D * H * H + e] = a2[e] * inv_n2;
-    // z: ghat[kz][ky][kx] / n^3
-    const double inv_n3 = 1.0 / (double(n) * n * n);
-    double* out = &ghat[size_t(li) * H * H * H];
-    for (int kz = 0; kz < H; ++kz)
-      for (int ky = 0; ky < H; ++ky)
-        for (int kx = 0; kx < H; ++kx) {
-          double acc = 0.0;
-          for (int z = 0; z < n; ++z) acc += a2[(size_t(z) * H + ky) * H + kx] * cs[size_t(kz) * n + z];
-          out[(size_t(kz) * H + ky) * H + kx] = acc * inv_n3;
-        }
-  }
   p.tab.ghat_levels = nlev;
-  if (p.prob.m2l_mode != HPM_M2L_GRID) {
-    const std::vector<double> gc = cell_green(p, nlev);
-    if (p.prec == HPM_F32) upload<float>(p.tab.gcell, gc, s);
-    else upload<double>(p.tab.gcell, gc, s);
-    p.tab.gcell_levels = nlev;
-  }
-  if (p.prec == HPM_F32) {
-    // e^{+2 pi i m / n} as float pairs (hi, lo) per component, for the all-FP32 inverse
-    // transform: {cos hi, sin hi, cos lo, sin lo}
-    const int nn = 8 * p.ng;
-    std::vector<double> tw(size_t(nn) * 4);
-    for (int m = 0; m < nn; ++m) {
-      const double c = std::cos(2.0 * M_PI * m / nn), sn = std::sin(2.0 * M_PI * m / nn);
-      const float ch = float(c), sh = float(sn);
-      tw[4 * m] = ch;
-      tw[4 * m + 1] = sh;
-      tw[4 * m + 2] = float(c - double(ch));
-      tw[4 * m + 3] = float(sn - double(sh));
-    }
-    upload<float>(p.tab.twff, tw, s);
-    upload<float>(p.tab.fitw, w, s);
-    upload<float>(p.tab.m2m, t1, s);
-    upload<float>(p.tab.l2l, t1l, s);
-    upload<float>(p.tab.ghat, ghat, s);
-    upload<float>(p.tab.gxy, gxy, s);
-  } else {
-    upload<double>(p.tab.fitw, w, s);
-    upload<double>(p.tab.m2m, t1, s);
-    upload<double>(p.tab.l2l, t1l, s);
-    upload<double>(p.tab.ghat, ghat, s);
-    upload<double>(p.tab.gxy, gxy, s);
-  }
+  if (p.prec == HPM_F32) tables_t<float>(p, nlev, small, cs, tg, s);
+  else tables_t<double>(p, nlev, small, cs, tg, s);
 }
 
 }  // namespace hpm
