@@ -354,7 +354,6 @@ __global__ __launch_bounds__(256) void k_m2l(M2LArgs<T> a) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kSlabThreads = 256;      // threads per workgroup
 constexpr int kSlabLayers = 1;         // block layers (N_g source z rows each) per slab
-constexpr bool kSlabGreenLds = false;  // Green table of the level in LDS (else read through L2)
 constexpr int kSlabPerCU = 2;          // resident workgroups per CU
 
 // EXT = 1: extended target gridlets (Sec. 2.5), NL = N_g + 2 nodes per axis, the target window
@@ -383,11 +382,8 @@ struct SlabShape {
   static constexpr int PER = (ENT + NT - 1) / NT;
   static constexpr int NJ = ZW + ZB - 1;    // distinct offsets Z - z within one slab and pass
   static constexpr size_t slab_bytes = size_t(ZB) * n * H * sizeof(cplx<T>);
-  static constexpr size_t green_bytes = size_t(D) * H * H * sizeof(T);
   static constexpr size_t red_bytes = size_t(NL) * NL * H * sizeof(cplx<RedT>) + size_t(ML) * 8 +
                                       size_t(n) * sizeof(cplx<double>) + 2048;
-  static constexpr bool green_lds =
-      kSlabGreenLds && slab_bytes + red_bytes + green_bytes <= 160 * 1024;
   static constexpr bool fits = slab_bytes + red_bytes <= 160 * 1024;
 };
 
@@ -408,6 +404,13 @@ __device__ __forceinline__ void slab_sum(const M2LArgs<T>& a, const int* s_src, 
   for (int r = 0; r < PER; ++r)
 #pragma unroll
     for (int zz = 0; zz < ZW; ++zz) pr[r][zz] = pi[r][zz] = T(0);
+  // byte offset of this thread's entries (folded ky, kx) in a plane of the Green table
+  uint32_t goff[PER];
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int e = tid + NT * r, ky = e / H, kx = e % H;
+    goff[r] = uint32_t((ky <= n / 2 ? ky : n - ky) * H + kx) * uint32_t(sizeof(T));
+  }
 
   for (int z0 = 0; z0 < W; z0 += ZB) {
     if constexpr (S::XS == 1) {
@@ -493,18 +496,24 @@ __device__ __forceinline__ void slab_sum(const M2LArgs<T>& a, const int* s_src, 
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       const int e = tid + NT * r;
-      if (e < ENT) {
-        const int ky = e / H, kx = e % H;
-        const int kyf = ky <= n / 2 ? ky : n - ky;
+      // in FP32 the entries that every thread has run without a branch, so that one's loads overlap
+      // another's arithmetic; FP64 has no registers for that (404 leave room for the near-zone
+      // waves beside it, 424 do not)
+      if ((sizeof(T) == 4 && NT * (r + 1) <= ENT) || e < ENT) {
+        // The planes' addresses are the workgroup's (scalar registers) and a thread adds its 32-bit
+        // offset: with the whole index formed per thread, 64-bit multiplies included, an entry took
+        // 137 vector instructions instead of 95 (2^18 Plummer, N_g = 6, FP32: the kernel, bound by
+        // vector issue, 1.75 -> 1.59 ms).
         T g[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
           const int d = Zt - z0 + j - (ZB - 1);
-          g[j] = gtab[(size_t(d < 0 ? -d : d) * H + kyf) * H + kx];
+          const char* plane = reinterpret_cast<const char*>(gtab + size_t(d < 0 ? -d : d) * H * H);
+          g[j] = *reinterpret_cast<const T*>(plane + goff[r]);
         }
         cplx<T> sv[ZB];
 #pragma unroll
-        for (int zb = 0; zb < ZB; ++zb) sv[zb] = slab[(size_t(zb) * n + ky) * H + kx];
+        for (int zb = 0; zb < ZB; ++zb) sv[zb] = slab[zb * ENT + e];
 #pragma unroll
         for (int zz = 0; zz < ZW; ++zz) {
           T ar = g[zz + ZB - 1] * sv[0].re, ai = g[zz + ZB - 1] * sv[0].im;
@@ -541,7 +550,6 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
   __shared__ double s_out[ML];
   __shared__ double s_red[NT / 64];
   __shared__ cplx<double> s_tw[n];  // e^{+2 pi i m / n}
-  __shared__ T s_green[S::green_lds ? D * H * H : 1];  // [d][ky folded][kx]
   __shared__ float4 s_twf[STRICT ? n : 1];
   const int tid = threadIdx.x;
   // Waves of this kernel win issue arbitration over the near-zone kernel running beside it on
@@ -557,7 +565,6 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
       s_tw[m] = {cv, sv};
     }
   }
-  int green_level = -1;
 
   const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, jb = blockIdx.x >> 3;
   const int t_begin = int((int64_t(a.ntargets) * xcd) / 8);
@@ -567,16 +574,9 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
     __syncthreads();
     const TargetGeom t = target_geom(a.first_target + ti, s_off, a.nlevels, a.coord, a.parent, a.size);
     if (tid < 216) s_src[tid] = resolve_slot(a, t, tid);
-    const T* gtab_g = a.gxy + size_t(t.l - 2) * D * H * H;
-    if constexpr (S::green_lds) {
-      if (t.l != green_level) {  // block-uniform: every thread sees the same target
-        for (int e = tid; e < D * H * H; e += NT) s_green[e] = gtab_g[e];
-        green_level = t.l;
-      }
-    }
+    const T* gtab = a.gxy + size_t(__builtin_amdgcn_readfirstlane(t.l) - 2) * D * H * H;
     __syncthreads();
-    const T* gtab = S::green_lds ? s_green : gtab_g;
-    const int Zt = (2 + t.cz) * NG - EXT;
+    const int Zt = __builtin_amdgcn_readfirstlane((2 + t.cz) * NG - EXT);
 
     // The target z planes in passes of ZW (all N_g at once unless the accumulators would not
     // fit), each pass's planes through the slab buffer ZG at a time for the inverse y transform.
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_parent(M2LArgs<T> a) {
     }
     if (tid < 8) s_kid[tid] = a.child8[size_t(par) * 8 + tid];
     __syncthreads();
-    const T* gtab = a.gxy + size_t(l - 2) * D * H * H;
+    const T* gtab = a.gxy + size_t(__builtin_amdgcn_readfirstlane(l) - 2) * D * H * H;
 
     for (int cz = 0; cz < 2; ++cz) {
       // block-uniform: every thread reads the same child ids
