@@ -151,8 +151,8 @@ void rebuild_plan(Plan& p, int64_t n, const void* x, const void* y, const void* 
     const size_t ntg = cells - size_t(p.level_off[2]);
     p.cell_src.reserve((ntg + size_t(p.nvirt) + 1) * spec);  // + a zero row
     p.cell_tgt.reserve(ntg * spec);
-    read_cell_parents(p);
   }
+  read_cell_parents(p);
   finish_near_lists(p, s);
   if (p.timing) {  // read when the next build starts or the times are asked for
     HPM_HIP(hipEventRecord(p.tree_ev[1], s));

@@ -23,6 +23,7 @@
 // masses fitted once per solve, beside the leaves'; they are found here by their cube id.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dev_common.h"
@@ -387,176 +388,330 @@ struct SlabShape {
   static constexpr bool fits = slab_bytes + red_bytes <= 160 * 1024;
 };
 
-// The slab loop of the z-slab scheme: every source z row of the 6 N_g block (the cubes of s_src)
-// through the x and y transforms in LDS and into the real-space z sum (pr, pi) at the ZW target
-// z values Zt .. Zt + ZW - 1. Called by all threads of the workgroup; the accumulators are
-// per thread, entry e = tid + NT r. tw holds e^{+2 pi i m / n}, m < n.
+// The x and y transforms of the ZB source z rows from z0 on (of the cubes of s_src), into the slab buffer
+// [zb][ky][kx]. Called by all threads of the workgroup; ends with a barrier. tw holds
+// e^{+2 pi i m / n}, m < n.
+template <typename T, int NG, int EXT>
+__device__ __forceinline__ void forward_slab(const M2LArgs<T>& a, const int* s_src, cplx<T>* slab, int z0,
+                                             const cplx<double>* tw) {
+  using S = SlabShape<T, NG, EXT>;
+  constexpr int n = S::n, H = S::H, W = S::W, NT = S::NT, ZB = S::ZB, YS = S::YS;
+  const int tid = threadIdx.x;
+  if constexpr (S::XS == 1) {
+    // x: rows (zb, y) of the slab, y fastest, one real row per thread
+    for (int w = tid; w < ZB * W; w += NT) {
+      const int zb = w / W, yr = w % W;
+      cplx<T> X[H];
+      xpass_row<T, NG>(a, yr, z0 + zb, s_src, X);
+      cplx<T>* row = slab + (size_t(zb) * n + yr) * H;
+#pragma unroll
+      for (int k = 0; k < H; ++k) row[k] = X[k];
+    }
+  } else {
+    // x: two threads per row, one per parity of the output frequency
+    for (int w = tid; w < ZB * W * 2; w += NT) {
+      const int q = w & 1, r = w >> 1;
+      const int zb = r / W, yr = r % W;
+      cplx<T>* row = slab + (size_t(zb) * n + yr) * H;
+      if (q == 0) xpass_row_half<T, NG, 0>(a, yr, z0 + zb, s_src, row);
+      else xpass_row_half<T, NG, 1>(a, yr, z0 + zb, s_src, row);
+    }
+  }
+  __syncthreads();
+  if constexpr (YS == 1) {
+    // y: columns (zb, kx); rows y >= 6 N_g are zero
+    for (int w = tid; w < ZB * H; w += NT) {
+      const int kx = w % H, zb = w / H;
+      cplx<T>* col = slab + size_t(zb) * n * H + kx;
+      cplx<T> in[n], out[n];
+#pragma unroll
+      for (int y = 0; y < n; ++y) in[y] = (y < W) ? col[size_t(y) * H] : cplx<T>{T(0), T(0)};
+      fft<n, -1>(in, out);
+#pragma unroll
+      for (int y = 0; y < n; ++y) col[size_t(y) * H] = out[y];
+    }
+  } else {
+    // y split over YS threads per column (decimation in frequency): thread q transforms
+    //   u_j = e^{-2 pi i q j / n} sum_r x_{j + r m} e^{-2 pi i q r / YS},  j < m = n / YS,
+    // whose m-point transform is the column's outputs ky = YS k + q. All threads read their
+    // inputs before any output is written back in place.
+    static_assert(YS == 4, "forward y split");
+    constexpr int m = n / YS, TASKS = ZB * H * YS;
+    for (int w0 = 0; w0 < TASKS; w0 += NT) {
+      const int w = w0 + tid;
+      const bool live = w < TASKS;
+      const int q = w % YS, c = w / YS;
+      const int kx = c % H, zb = c / H;
+      cplx<T>* col = slab + size_t(zb) * n * H + kx;
+      cplx<T> u[m], out[m];
+      if (live) {
+#pragma unroll
+        for (int j = 0; j < m; ++j) {
+          cplx<T> acc = {T(0), T(0)};
+#pragma unroll
+          for (int r = 0; r < YS; ++r) {
+            if (j + r * m < W) {
+              const cplx<T> v = col[size_t(j + r * m) * H];
+              // times (-i)^(q r)
+              switch ((q * r) & 3) {
+                case 0: acc = cadd(acc, v); break;
+                case 1: acc = cadd(acc, cplx<T>{v.im, -v.re}); break;
+                case 2: acc = csub(acc, v); break;
+                default: acc = cadd(acc, cplx<T>{-v.im, v.re}); break;
+              }
+            }
+          }
+          const cplx<double> t = tw[(q * j) % n];
+          u[j] = cmul(acc, cplx<T>{T(t.re), T(-t.im)});
+        }
+        fft<m, -1>(u, out);
+      }
+      __syncthreads();
+      if (live) {
+#pragma unroll
+        for (int k = 0; k < m; ++k) col[size_t(YS * k + q) * H] = out[k];
+      }
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+}
+
+// byte offsets of this thread's entries (folded ky, kx), e = tid + NT r, in a plane of the Green table
+template <typename T, int NG, int EXT>
+__device__ __forceinline__ void green_offsets(uint32_t* goff) {
+  using S = SlabShape<T, NG, EXT>;
+#pragma unroll
+  for (int r = 0; r < S::PER; ++r) {
+    const int e = int(threadIdx.x) + S::NT * r, ky = e / S::H, kx = e % S::H;
+    goff[r] = uint32_t((ky <= S::n / 2 ? ky : S::n - ky) * S::H + kx) * uint32_t(sizeof(T));
+  }
+}
+
+// The slab's part of the real-space z sum (pr, pi) at the ZW target z values Zt .. Zt + ZW - 1; the
+// accumulators are per thread, entry e = tid + NT r.
+template <typename T, int NG, int EXT>
+__device__ __forceinline__ void accumulate_slab(const cplx<T>* slab, const T* gtab, int Zt, int z0,
+                                                const uint32_t (&goff)[SlabShape<T, NG, EXT>::PER],
+                                                T (&pr)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
+                                                T (&pi)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW]) {
+  using S = SlabShape<T, NG, EXT>;
+  constexpr int H = S::H, NT = S::NT, ZB = S::ZB, ZW = S::ZW, PER = S::PER, NJ = S::NJ, ENT = S::ENT;
+  const int tid = threadIdx.x;
+  // z in real space: P(Z) += sum_zb Gxy(|Zt + Z - z0 - zb|) S(zb) for this slab, the slab's
+  // terms chained with FMAs before they join the running sum
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int e = tid + NT * r;
+    // in FP32 the entries that every thread has run without a branch, so that one's loads overlap
+    // another's arithmetic; FP64 has no registers for that (404 leave room for the near-zone
+    // waves beside it, 424 do not)
+    if ((sizeof(T) == 4 && NT * (r + 1) <= ENT) || e < ENT) {
+      // The planes' addresses are the workgroup's (scalar registers) and a thread adds its 32-bit
+      // offset: with the whole index formed per thread, 64-bit multiplies included, an entry took
+      // 137 vector instructions instead of 95 (2^18 Plummer, N_g = 6, FP32: the kernel, bound by
+      // vector issue, 1.75 -> 1.59 ms).
+      T g[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int d = Zt - z0 + j - (ZB - 1);
+        const char* plane = reinterpret_cast<const char*>(gtab + size_t(d < 0 ? -d : d) * H * H);
+        g[j] = *reinterpret_cast<const T*>(plane + goff[r]);
+      }
+      cplx<T> sv[ZB];
+#pragma unroll
+      for (int zb = 0; zb < ZB; ++zb) sv[zb] = slab[zb * ENT + e];
+#pragma unroll
+      for (int zz = 0; zz < ZW; ++zz) {
+        T ar = g[zz + ZB - 1] * sv[0].re, ai = g[zz + ZB - 1] * sv[0].im;
+#pragma unroll
+        for (int zb = 1; zb < ZB; ++zb) {
+          const T gv = g[zz - zb + ZB - 1];
+          ar = fma(gv, sv[zb].re, ar);
+          ai = fma(gv, sv[zb].im, ai);
+        }
+        pr[r][zz] += ar;
+        pi[r][zz] += ai;
+      }
+    }
+  }
+}
+
+// The slab loop of the z-slab scheme: every source z row of the 6 N_g block (the cubes of s_src).
 template <typename T, int NG, int EXT = 0>
 __device__ __forceinline__ void slab_sum(const M2LArgs<T>& a, const int* s_src, cplx<T>* slab,
                                          const T* gtab, int Zt, const cplx<double>* tw,
                                          T (&pr)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
                                          T (&pi)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW]) {
   using S = SlabShape<T, NG, EXT>;
-  constexpr int n = S::n, H = S::H, W = S::W, NT = S::NT, ZB = S::ZB, ZW = S::ZW, YS = S::YS,
-                PER = S::PER, NJ = S::NJ, ENT = S::ENT;
+  uint32_t goff[S::PER];
+  green_offsets<T, NG, EXT>(goff);
+#pragma unroll
+  for (int r = 0; r < S::PER; ++r)
+#pragma unroll
+    for (int zz = 0; zz < S::ZW; ++zz) pr[r][zz] = pi[r][zz] = T(0);
+  for (int z0 = 0; z0 < S::W; z0 += S::ZB) {
+    forward_slab<T, NG, EXT>(a, s_src, slab, z0, tw);
+    accumulate_slab<T, NG, EXT>(slab, gtab, Zt, z0, goff, pr, pi);
+    __syncthreads();
+  }
+}
+
+// Inverse y transform of a pass's accumulated planes (all threads; the slab buffer takes ZG planes at
+// a time): red[Z][yy][kx] for the N_g target y values of octant half cy, the planes from zp on.
+template <typename T, int NG, int EXT>
+__device__ __forceinline__ void inverse_y(const T (&pr)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
+                                          const T (&pi)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
+                                          cplx<T>* slab, cplx<typename SlabShape<T, NG, EXT>::RedT>* red,
+                                          const cplx<double>* s_tw, int zp, int cy) {
+  using S = SlabShape<T, NG, EXT>;
+  constexpr int n = S::n, H = S::H, NT = S::NT, PER = S::PER, ENT = S::ENT, ZW = S::ZW, ZG = S::ZG,
+                NL = S::NL;
   const int tid = threadIdx.x;
 #pragma unroll
-  for (int r = 0; r < PER; ++r)
-#pragma unroll
-    for (int zz = 0; zz < ZW; ++zz) pr[r][zz] = pi[r][zz] = T(0);
-  // byte offset of this thread's entries (folded ky, kx) in a plane of the Green table
-  uint32_t goff[PER];
-#pragma unroll
-  for (int r = 0; r < PER; ++r) {
-    const int e = tid + NT * r, ky = e / H, kx = e % H;
-    goff[r] = uint32_t((ky <= n / 2 ? ky : n - ky) * H + kx) * uint32_t(sizeof(T));
-  }
-
-  for (int z0 = 0; z0 < W; z0 += ZB) {
-    if constexpr (S::XS == 1) {
-      // x: rows (zb, y) of the slab, y fastest, one real row per thread
-      for (int w = tid; w < ZB * W; w += NT) {
-        const int zb = w / W, yr = w % W;
-        cplx<T> X[H];
-        xpass_row<T, NG>(a, yr, z0 + zb, s_src, X);
-        cplx<T>* row = slab + (size_t(zb) * n + yr) * H;
-#pragma unroll
-        for (int k = 0; k < H; ++k) row[k] = X[k];
-      }
-    } else {
-      // x: two threads per row, one per parity of the output frequency
-      for (int w = tid; w < ZB * W * 2; w += NT) {
-        const int q = w & 1, r = w >> 1;
-        const int zb = r / W, yr = r % W;
-        cplx<T>* row = slab + (size_t(zb) * n + yr) * H;
-        if (q == 0) xpass_row_half<T, NG, 0>(a, yr, z0 + zb, s_src, row);
-        else xpass_row_half<T, NG, 1>(a, yr, z0 + zb, s_src, row);
-      }
-    }
-    __syncthreads();
-    if constexpr (YS == 1) {
-      // y: columns (zb, kx); rows y >= 6 N_g are zero
-      for (int w = tid; w < ZB * H; w += NT) {
-        const int kx = w % H, zb = w / H;
-        cplx<T>* col = slab + size_t(zb) * n * H + kx;
-        cplx<T> in[n], out[n];
-#pragma unroll
-        for (int y = 0; y < n; ++y) in[y] = (y < W) ? col[size_t(y) * H] : cplx<T>{T(0), T(0)};
-        fft<n, -1>(in, out);
-#pragma unroll
-        for (int y = 0; y < n; ++y) col[size_t(y) * H] = out[y];
-      }
-    } else {
-      // y split over YS threads per column (decimation in frequency): thread q transforms
-      //   u_j = e^{-2 pi i q j / n} sum_r x_{j + r m} e^{-2 pi i q r / YS},  j < m = n / YS,
-      // whose m-point transform is the column's outputs ky = YS k + q. All threads read their
-      // inputs before any output is written back in place.
-      static_assert(YS == 4, "forward y split");
-      constexpr int m = n / YS, TASKS = ZB * H * YS;
-      for (int w0 = 0; w0 < TASKS; w0 += NT) {
-        const int w = w0 + tid;
-        const bool live = w < TASKS;
-        const int q = w % YS, c = w / YS;
-        const int kx = c % H, zb = c / H;
-        cplx<T>* col = slab + size_t(zb) * n * H + kx;
-        cplx<T> u[m], out[m];
-        if (live) {
-#pragma unroll
-          for (int j = 0; j < m; ++j) {
-            cplx<T> acc = {T(0), T(0)};
-#pragma unroll
-            for (int r = 0; r < YS; ++r) {
-              if (j + r * m < W) {
-                const cplx<T> v = col[size_t(j + r * m) * H];
-                // times (-i)^(q r)
-                switch ((q * r) & 3) {
-                  case 0: acc = cadd(acc, v); break;
-                  case 1: acc = cadd(acc, cplx<T>{v.im, -v.re}); break;
-                  case 2: acc = csub(acc, v); break;
-                  default: acc = cadd(acc, cplx<T>{-v.im, v.re}); break;
-                }
-              }
-            }
-            const cplx<double> t = tw[(q * j) % n];
-            u[j] = cmul(acc, cplx<T>{T(t.re), T(-t.im)});
-          }
-          fft<m, -1>(u, out);
-        }
-        __syncthreads();
-        if (live) {
-#pragma unroll
-          for (int k = 0; k < m; ++k) col[size_t(YS * k + q) * H] = out[k];
-        }
-        __syncthreads();
-      }
-    }
-    __syncthreads();
-    // z in real space: P(Z) += sum_zb Gxy(|Zt + Z - z0 - zb|) S(zb) for this slab, the slab's
-    // terms chained with FMAs before they join the running sum
+  for (int z0 = 0; z0 < ZW; z0 += ZG) {
+    const int zg = ZW - z0 < ZG ? ZW - z0 : ZG;  // planes in this group
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       const int e = tid + NT * r;
-      // in FP32 the entries that every thread has run without a branch, so that one's loads overlap
-      // another's arithmetic; FP64 has no registers for that (404 leave room for the near-zone
-      // waves beside it, 424 do not)
-      if ((sizeof(T) == 4 && NT * (r + 1) <= ENT) || e < ENT) {
-        // The planes' addresses are the workgroup's (scalar registers) and a thread adds its 32-bit
-        // offset: with the whole index formed per thread, 64-bit multiplies included, an entry took
-        // 137 vector instructions instead of 95 (2^18 Plummer, N_g = 6, FP32: the kernel, bound by
-        // vector issue, 1.75 -> 1.59 ms).
-        T g[NJ];
+      if (e < ENT) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          const int d = Zt - z0 + j - (ZB - 1);
-          const char* plane = reinterpret_cast<const char*>(gtab + size_t(d < 0 ? -d : d) * H * H);
-          g[j] = *reinterpret_cast<const T*>(plane + goff[r]);
+        for (int zz = 0; zz < ZG; ++zz)
+          if (z0 + zz < ZW) slab[size_t(zz) * ENT + e] = {pr[r][z0 + zz], pi[r][z0 + zz]};
+      }
+    }
+    __syncthreads();
+    // y^-1: red[Z][yy][kx] = sum_ky P(Z, ky, kx) e^{+2 pi i ky Y / n},
+    // Y = (2 + c_y) N_g - EXT + yy
+    if constexpr (!S::wide) {
+      for (int w = tid; w < zg * H; w += NT) {
+        const int kx = w % H, zz = w / H;
+        const cplx<T>* col = slab + size_t(zz) * ENT + kx;
+        cplx<T> in[n], out[n];
+#pragma unroll
+        for (int y = 0; y < n; ++y) in[y] = col[size_t(y) * H];
+        fft<n, +1>(in, out);
+#pragma unroll
+        for (int yy = 0; yy < NL; ++yy) {
+          const cplx<T> o0 = out[2 * NG - EXT + yy], o1 = out[3 * NG - EXT + yy];
+          red[(size_t(zp + z0 + zz) * NL + yy) * H + kx] = {cy ? o1.re : o0.re, cy ? o1.im : o0.im};
         }
-        cplx<T> sv[ZB];
-#pragma unroll
-        for (int zb = 0; zb < ZB; ++zb) sv[zb] = slab[zb * ENT + e];
-#pragma unroll
-        for (int zz = 0; zz < ZW; ++zz) {
-          T ar = g[zz + ZB - 1] * sv[0].re, ai = g[zz + ZB - 1] * sv[0].im;
-#pragma unroll
-          for (int zb = 1; zb < ZB; ++zb) {
-            const T gv = g[zz - zb + ZB - 1];
-            ar = fma(gv, sv[zb].re, ar);
-            ai = fma(gv, sv[zb].im, ai);
-          }
-          pr[r][zz] += ar;
-          pi[r][zz] += ai;
+      }
+    } else {
+      // pruned: only the N_g target values of each column, as direct sums in double
+      for (int w = tid; w < zg * H * NL; w += NT) {
+        const int kx = w % H, yy = (w / H) % NL, zz = w / (H * NL);
+        const int Y = (2 + cy) * NG - EXT + yy;
+        const cplx<T>* col = slab + size_t(zz) * ENT + kx;
+        cplx<double> acc = {0.0, 0.0};
+        int mi = 0;
+#pragma unroll 8
+        for (int ky = 0; ky < n; ++ky) {
+          const cplx<double> tv = s_tw[mi];
+          const cplx<T> f = col[size_t(ky) * H];
+          acc.re = fma(double(f.re), tv.re, fma(-double(f.im), tv.im, acc.re));
+          acc.im = fma(double(f.re), tv.im, fma(double(f.im), tv.re, acc.im));
+          mi += Y;
+          if (mi >= n) mi -= n;
         }
+        red[(size_t(zp + z0 + zz) * NL + yy) * H + kx] = acc;
       }
     }
     __syncthreads();
   }
 }
 
+// Inverse x transform of target g from red (all threads), its mean and its zero-mean gridlet.
 // STRICT (FP32 plans, N_g = 4 and 6): the inverse x sums and the mean in float-float arithmetic
 // against float-float twiddles from the tables, the mean stored as a float pair; no FP64
 // arithmetic in the kernel.
-template <typename T, int NG, int EXT, bool STRICT = false>
-__global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
+template <typename T, int NG, int EXT, bool STRICT>
+__device__ __forceinline__ void inverse_x(const M2LArgs<T>& a, int g, int cx,
+                                          const cplx<typename SlabShape<T, NG, EXT>::RedT>* red,
+                                          const cplx<double>* s_tw, const float4* s_twf, double* s_out,
+                                          double* s_red) {
   using S = SlabShape<T, NG, EXT>;
   static_assert(!STRICT || (sizeof(T) == 4 && !S::wide), "float-float inverse: FP32, N_g <= 6");
-  constexpr int n = S::n, H = S::H, NT = S::NT, D = S::D, PER = S::PER, ENT = S::ENT,
-                ZW = S::ZW, ZG = S::ZG, NL = S::NL, ML = S::ML;
-  static_assert(S::fits, "slab buffers exceed the LDS budget");
-  static_assert(S::W % S::ZB == 0 && S::W % 2 == 0 && NL % ZW == 0, "slab shape");
-  __shared__ int s_src[216];
-  __shared__ int s_off[kMaxLevels + 1];
-  __shared__ __align__(16) cplx<T> slab[S::ZB * n * H];  // [zb][ky (y before the y pass)][kx]
-  __shared__ cplx<typename S::RedT> red[NL * NL * H];    // after y^-1: [Z][Y][kx]
-  __shared__ double s_out[ML];
-  __shared__ double s_red[NT / 64];
-  __shared__ cplx<double> s_tw[n];  // e^{+2 pi i m / n}
-  __shared__ float4 s_twf[STRICT ? n : 1];
+  constexpr int n = S::n, H = S::H, NT = S::NT, NL = S::NL, ML = S::ML;
   const int tid = threadIdx.x;
-  // Waves of this kernel win issue arbitration over the near-zone kernel running beside it on
-  // the second stream (measured: 1% off the solve, and off this kernel alone as well).
-  __builtin_amdgcn_s_setprio(2);
-  if (tid <= kMaxLevels) s_off[tid] = a.level_off[tid];
-  for (int m = tid; m < n; m += NT) {
+  // x^-1 (Hermitian half spectrum): out = sum_k w_k Re(F_k e^{+2 pi i k X / n}), w_k = 1 at
+  // k = 0 and n/2, 2 otherwise; X = (2 + c_x) N_g - EXT + xx
+  const int Xt = (2 + cx) * NG - EXT;
+  if constexpr (STRICT) {
+    // the same sums in float-float: each product of a float spectrum value and a float-float
+    // twiddle formed exactly to float-float precision, the terms added with renormalisation
+    ff32* s_outf = reinterpret_cast<ff32*>(s_out);
+    for (int q = tid; q < ML; q += NT) {
+      const int xx = q % NL, row = q / NL;
+      const int X = Xt + xx;
+      const cplx<typename S::RedT>* F = red + size_t(row) * H;
+      ff32 acc = {0.0f, 0.0f};
+      int m = 0;
+      for (int k = 0; k < H; ++k) {
+        const float4 w = s_twf[m];
+        ff32 v = ff_add(ff_mul(float(F[k].re), ff32{w.x, w.z}),
+                        ff_neg(ff_mul(float(F[k].im), ff32{w.y, w.w})));
+        if (!(k == 0 || k == n / 2)) v = {2.0f * v.hi, 2.0f * v.lo};
+        acc = ff_add(acc, v);
+        m += X;
+        if (m >= n) m -= n;
+      }
+      s_outf[q] = acc;
+    }
+    __syncthreads();
+    // result = mean (a float pair, per target) + zero-mean gridlet
+    ff32* s_redf = reinterpret_cast<ff32*>(s_red);
+    ff32 part = {0.0f, 0.0f};
+    for (int e = tid; e < ML; e += NT) part = ff_add(part, s_outf[e]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+      part = ff_add(part, ff32{__shfl_xor(part.hi, o, 64), __shfl_xor(part.lo, o, 64)});
+    if ((tid & 63) == 0) s_redf[tid >> 6] = part;
+    __syncthreads();
+    ff32 sum = {0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sum = ff_add(sum, s_redf[w]);
+    const ff32 mean = ff_div(sum, ML);
+    for (int e = tid; e < ML; e += NT)
+      a.local[size_t(g) * ML + e] = ff_add(s_outf[e], ff_neg(mean)).hi;
+    if (tid == 0) reinterpret_cast<ff32*>(a.m2l_mean)[g] = mean;
+  } else {
+    for (int q = tid; q < ML; q += NT) {
+      const int xx = q % NL, row = q / NL;
+      const int X = Xt + xx;
+      const cplx<typename S::RedT>* F = red + size_t(row) * H;
+      double acc = 0.0;
+      int m = 0;
+      for (int k = 0; k < H; ++k) {
+        const cplx<double> f = {double(F[k].re), double(F[k].im)};
+        const cplx<double> w = s_tw[m];
+        const double v = f.re * w.re - f.im * w.im;
+        acc += (k == 0 || k == n / 2) ? v : 2.0 * v;
+        m += X;
+        if (m >= n) m -= n;
+      }
+      s_out[q] = acc;
+    }
+    __syncthreads();
+    // result = mean (double, per target) + zero-mean gridlet (T)
+    double part = 0.0;
+    for (int e = tid; e < ML; e += NT) part += s_out[e];
+    part = wave_sum(part);
+    if ((tid & 63) == 0) s_red[tid >> 6] = part;
+    __syncthreads();
+    double mean = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) mean += s_red[w];
+    mean *= 1.0 / ML;
+    for (int e = tid; e < ML; e += NT) a.local[size_t(g) * ML + e] = T(s_out[e] - mean);
+    if (tid == 0) a.m2l_mean[g] = mean;
+  }
+}
+
+// the inverse transforms' twiddles: e^{+2 pi i m / n} in double, or float-float from the tables
+template <typename T, int n, int NT, bool STRICT>
+__device__ __forceinline__ void load_inverse_twiddles(const M2LArgs<T>& a, cplx<double>* s_tw, float4* s_twf) {
+  for (int m = threadIdx.x; m < n; m += NT) {
     if constexpr (STRICT) {
       s_twf[m] = a.twff[m];
     } else {
@@ -565,6 +720,30 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
       s_tw[m] = {cv, sv};
     }
   }
+}
+
+// One target at a time: small trees, and N_g = 8 and FP64 N_g = 6, where a second child's accumulators
+// do not fit.
+template <typename T, int NG, int EXT, bool STRICT = false>
+__global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
+  using S = SlabShape<T, NG, EXT>;
+  constexpr int n = S::n, H = S::H, NT = S::NT, D = S::D, PER = S::PER, ZW = S::ZW, NL = S::NL, ML = S::ML;
+  static_assert(S::fits, "slab buffers exceed the LDS budget");
+  static_assert(S::W % S::ZB == 0 && S::W % 2 == 0 && NL % ZW == 0, "slab shape");
+  __shared__ int s_src[216];
+  __shared__ int s_off[kMaxLevels + 1];
+  __shared__ __align__(16) cplx<T> slab[S::ZB * n * H];  // [zb][ky (y before the y pass)][kx]
+  __shared__ cplx<typename S::RedT> red[NL * NL * H];    // after y^-1: [Z][Y][kx]
+  __shared__ double s_out[ML];
+  __shared__ double s_red[NT / 64];
+  __shared__ cplx<double> s_tw[STRICT ? 1 : n];  // e^{+2 pi i m / n}
+  __shared__ float4 s_twf[STRICT ? n : 1];
+  const int tid = threadIdx.x;
+  // Waves of this kernel win issue arbitration over the near-zone kernel running beside it on
+  // the second stream (measured: 1% off the solve, and off this kernel alone as well).
+  __builtin_amdgcn_s_setprio(2);
+  if (tid <= kMaxLevels) s_off[tid] = a.level_off[tid];
+  load_inverse_twiddles<T, n, NT, STRICT>(a, s_tw, s_twf);
 
   const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, jb = blockIdx.x >> 3;
   const int t_begin = int((int64_t(a.ntargets) * xcd) / 8);
@@ -587,129 +766,88 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
     for (int zp = 0; zp < NL; zp += ZW) {
       T pr[PER][ZW], pi[PER][ZW];
       slab_sum<T, NG, EXT>(a, s_src, slab, gtab, Zt + zp, s_tw, pr, pi);
-#pragma unroll
-      for (int z0 = 0; z0 < ZW; z0 += ZG) {
-        const int zg = ZW - z0 < ZG ? ZW - z0 : ZG;  // planes in this group
-#pragma unroll
-        for (int r = 0; r < PER; ++r) {
-          const int e = tid + NT * r;
-          if (e < ENT) {
-#pragma unroll
-            for (int zz = 0; zz < ZG; ++zz)
-              if (z0 + zz < ZW) slab[size_t(zz) * ENT + e] = {pr[r][z0 + zz], pi[r][z0 + zz]};
-          }
-        }
-        __syncthreads();
-        // y^-1: red[Z][yy][kx] = sum_ky P(Z, ky, kx) e^{+2 pi i ky Y / n},
-        // Y = (2 + c_y) N_g - EXT + yy
-        if constexpr (!S::wide) {
-          for (int w = tid; w < zg * H; w += NT) {
-            const int kx = w % H, zz = w / H;
-            const cplx<T>* col = slab + size_t(zz) * ENT + kx;
-            cplx<T> in[n], out[n];
-#pragma unroll
-            for (int y = 0; y < n; ++y) in[y] = col[size_t(y) * H];
-            fft<n, +1>(in, out);
-#pragma unroll
-            for (int yy = 0; yy < NL; ++yy) {
-              const cplx<T> o0 = out[2 * NG - EXT + yy], o1 = out[3 * NG - EXT + yy];
-              red[(size_t(zp + z0 + zz) * NL + yy) * H + kx] = {t.cy ? o1.re : o0.re, t.cy ? o1.im : o0.im};
-            }
-          }
-        } else {
-          // pruned: only the N_g target values of each column, as direct sums in double
-          for (int w = tid; w < zg * H * NL; w += NT) {
-            const int kx = w % H, yy = (w / H) % NL, zz = w / (H * NL);
-            const int Y = (2 + t.cy) * NG - EXT + yy;
-            const cplx<T>* col = slab + size_t(zz) * ENT + kx;
-            cplx<double> acc = {0.0, 0.0};
-            int mi = 0;
-#pragma unroll 8
-            for (int ky = 0; ky < n; ++ky) {
-              const cplx<double> tv = s_tw[mi];
-              const cplx<T> f = col[size_t(ky) * H];
-              acc.re = fma(double(f.re), tv.re, fma(-double(f.im), tv.im, acc.re));
-              acc.im = fma(double(f.re), tv.im, fma(double(f.im), tv.re, acc.im));
-              mi += Y;
-              if (mi >= n) mi -= n;
-            }
-            red[(size_t(zp + z0 + zz) * NL + yy) * H + kx] = acc;
-          }
-        }
-        __syncthreads();
-      }
+      inverse_y<T, NG, EXT>(pr, pi, slab, red, s_tw, zp, t.cy);
     }
-    // x^-1 (Hermitian half spectrum): out = sum_k w_k Re(F_k e^{+2 pi i k X / n}), w_k = 1 at
-    // k = 0 and n/2, 2 otherwise; X = (2 + c_x) N_g - EXT + xx
-    const int Xt = (2 + t.cx) * NG - EXT;
-    if constexpr (STRICT) {
-      // the same sums in float-float: each product of a float spectrum value and a float-float
-      // twiddle formed exactly to float-float precision, the terms added with renormalisation
-      ff32* s_outf = reinterpret_cast<ff32*>(s_out);
-      for (int q = tid; q < ML; q += NT) {
-        const int xx = q % NL, row = q / NL;
-        const int X = Xt + xx;
-        const cplx<typename S::RedT>* F = red + size_t(row) * H;
-        ff32 acc = {0.0f, 0.0f};
-        int m = 0;
-        for (int k = 0; k < H; ++k) {
-          const float4 w = s_twf[m];
-          ff32 v = ff_add(ff_mul(float(F[k].re), ff32{w.x, w.z}),
-                          ff_neg(ff_mul(float(F[k].im), ff32{w.y, w.w})));
-          if (!(k == 0 || k == n / 2)) v = {2.0f * v.hi, 2.0f * v.lo};
-          acc = ff_add(acc, v);
-          m += X;
-          if (m >= n) m -= n;
-        }
-        s_outf[q] = acc;
-      }
-      __syncthreads();
-      // result = mean (a float pair, per target) + zero-mean gridlet
-      ff32* s_redf = reinterpret_cast<ff32*>(s_red);
-      ff32 part = {0.0f, 0.0f};
-      for (int e = tid; e < ML; e += NT) part = ff_add(part, s_outf[e]);
+    inverse_x<T, NG, EXT, STRICT>(a, t.g, t.cx, red, s_tw, s_twf, s_out, s_red);
+  }
+}
+
+// Two siblings at a time: the children (cx, cy, 0) and (cx, cy, 1) of a split parent. A block layer bz
+// is near (its cubes with bx, by near are left out) or far (whole) for each of them, and both read the
+// same 6^3 block, so the x and y transforms of layers 0 and 5 (far) and 2 and 3 (near) serve both: 8
+// transforms of a layer for two targets instead of 12. What each target gets is, operation for
+// operation, what it would get alone: its layers' transforms in order, its own z sum and inverse.
+// The transforms are two thirds of the vector instructions that bound the kernel. 2^18 Plummer, N_g =
+// 6, FP32: 1.59 -> 1.28 ms against one target at a time. Two workgroups per CU, as alone, although the
+// second accumulators then spill up to 40 registers of a thread (N_g = 4, FP64, 483 parents: 236 us, with
+// one workgroup per CU and no spills 322 us); with the extended gridlet at N_g = 6 one fits.
+template <typename T, int NG, int EXT, bool STRICT = false>
+__global__ __launch_bounds__(kSlabThreads, (NG == 6 && EXT ? 1 : 2)) void k_m2l_pair(M2LArgs<T> a) {
+  using S = SlabShape<T, NG, EXT>;
+  constexpr int n = S::n, H = S::H, NT = S::NT, D = S::D, PER = S::PER, ZW = S::ZW, NL = S::NL, ML = S::ML;
+  static_assert(S::fits, "slab buffers exceed the LDS budget");
+  static_assert(S::ZB == NG && ZW == NL && !S::wide, "a slab is a block layer, all planes in one pass");
+  __shared__ int s_src[2][216];  // the block's sources: all; without the cubes near in x and y
+  __shared__ int s_kid[2];
+  __shared__ int s_off[kMaxLevels + 1];
+  __shared__ __align__(16) cplx<T> slab[S::ZB * n * H];  // [zb][ky (y before the y pass)][kx]
+  __shared__ cplx<T> red[NL * NL * H];                   // after y^-1: [Z][Y][kx]
+  __shared__ double s_out[ML];
+  __shared__ double s_red[NT / 64];
+  __shared__ cplx<double> s_tw[STRICT ? 1 : n];  // e^{+2 pi i m / n}
+  __shared__ float4 s_twf[STRICT ? n : 1];
+  const int tid = threadIdx.x;
+  __builtin_amdgcn_s_setprio(2);  // over the near-zone kernel's waves beside it, as above
+  if (tid <= kMaxLevels) s_off[tid] = a.level_off[tid];
+  load_inverse_twiddles<T, n, NT, STRICT>(a, s_tw, s_twf);
+  uint32_t goff[PER];
+  green_offsets<T, NG, EXT>(goff);
+
+  // items: (parent, cx, cy), parents in Morton order, contiguous chunks per XCD
+  const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, jb = blockIdx.x >> 3;
+  const int total = a.nparents * 4;
+  const int i_begin = int((int64_t(total) * xcd) / 8), i_end = int((int64_t(total) * (xcd + 1)) / 8);
+  for (int it = i_begin + jb; it < i_end; it += per) {
+    __syncthreads();
+    const int par = a.plist[it >> 2];
+    const int cx = it & 1, cy = (it >> 1) & 1;
+    const int l = level_of(par, s_off, a.nlevels) + 1;  // the children's level (>= 2)
+    if (tid < 216) {
+      const int bx = tid % 6, by = (tid / 6) % 6;
+      const int src = a.blocks[size_t(par - a.first_parent) * 216 + tid];
+      s_src[0][tid] = src;
+      s_src[1][tid] = abs(bx - 2 - cx) <= 1 && abs(by - 2 - cy) <= 1 ? -1 : src;
+    }
+    if (tid < 2) s_kid[tid] = a.child8[size_t(par) * 8 + (cx | (cy << 1) | (tid << 2))];
+    __syncthreads();
+    const int kid0 = __builtin_amdgcn_readfirstlane(s_kid[0]);
+    const int kid1 = __builtin_amdgcn_readfirstlane(s_kid[1]);
+    if (kid0 < 0 && kid1 < 0) continue;
+    const T* gtab = a.gxy + size_t(__builtin_amdgcn_readfirstlane(l) - 2) * D * H * H;
+    T pr0[PER][ZW], pi0[PER][ZW], pr1[PER][ZW], pi1[PER][ZW];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1)
-        part = ff_add(part, ff32{__shfl_xor(part.hi, o, 64), __shfl_xor(part.lo, o, 64)});
-      if ((tid & 63) == 0) s_redf[tid >> 6] = part;
-      __syncthreads();
-      ff32 sum = {0.0f, 0.0f};
+    for (int r = 0; r < PER; ++r)
 #pragma unroll
-      for (int w = 0; w < NT / 64; ++w) sum = ff_add(sum, s_redf[w]);
-      const ff32 mean = ff_div(sum, ML);
-      for (int e = tid; e < ML; e += NT)
-        a.local[size_t(t.g) * ML + e] = ff_add(s_outf[e], ff_neg(mean)).hi;
-      if (tid == 0) reinterpret_cast<ff32*>(a.m2l_mean)[t.g] = mean;
-    } else {
-      for (int q = tid; q < ML; q += NT) {
-        const int xx = q % NL, row = q / NL;
-        const int X = Xt + xx;
-        const cplx<typename S::RedT>* F = red + size_t(row) * H;
-        double acc = 0.0;
-        int m = 0;
-        for (int k = 0; k < H; ++k) {
-          const cplx<double> f = {double(F[k].re), double(F[k].im)};
-          const cplx<double> w = s_tw[m];
-          const double v = f.re * w.re - f.im * w.im;
-          acc += (k == 0 || k == n / 2) ? v : 2.0 * v;
-          m += X;
-          if (m >= n) m -= n;
-        }
-        s_out[q] = acc;
-      }
+      for (int zz = 0; zz < ZW; ++zz) pr0[r][zz] = pi0[r][zz] = pr1[r][zz] = pi1[r][zz] = T(0);
+    // steps (layer, near): every condition is the workgroup's
+    for (int st = 0; st < 12; ++st) {
+      const int bz = st >> 1, near = st & 1;
+      const bool use0 = kid0 >= 0 && (bz >= 1 && bz <= 3) == (near != 0);
+      const bool use1 = kid1 >= 0 && (bz >= 2 && bz <= 4) == (near != 0);
+      if (!use0 && !use1) continue;
+      forward_slab<T, NG, EXT>(a, s_src[near], slab, bz * NG, s_tw);
+      if (use0) accumulate_slab<T, NG, EXT>(slab, gtab, 2 * NG - EXT, bz * NG, goff, pr0, pi0);
+      if (use1) accumulate_slab<T, NG, EXT>(slab, gtab, 3 * NG - EXT, bz * NG, goff, pr1, pi1);
       __syncthreads();
-      // result = mean (double, per target) + zero-mean gridlet (T)
-      double part = 0.0;
-      for (int e = tid; e < ML; e += NT) part += s_out[e];
-      part = wave_sum(part);
-      if ((tid & 63) == 0) s_red[tid >> 6] = part;
-      __syncthreads();
-      double mean = 0.0;
-#pragma unroll
-      for (int w = 0; w < NT / 64; ++w) mean += s_red[w];
-      mean *= 1.0 / ML;
-      for (int e = tid; e < ML; e += NT) a.local[size_t(t.g) * ML + e] = T(s_out[e] - mean);
-      if (tid == 0) a.m2l_mean[t.g] = mean;
+    }
+    if (kid0 >= 0) {
+      inverse_y<T, NG, EXT>(pr0, pi0, slab, red, s_tw, 0, cy);
+      inverse_x<T, NG, EXT, STRICT>(a, kid0, cx, red, s_tw, s_twf, s_out, s_red);
+      __syncthreads();  // red, s_out and s_red are reused
+    }
+    if (kid1 >= 0) {
+      inverse_y<T, NG, EXT>(pr1, pi1, slab, red, s_tw, 0, cy);
+      inverse_x<T, NG, EXT, STRICT>(a, kid1, cx, red, s_tw, s_twf, s_out, s_red);
     }
   }
 }
@@ -717,11 +855,13 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
 // ---------------------------------------------------------------------------------------------
 // The transform shared by the children of one split parent. Every child's interaction zone lies
 // in the parent's 6^3 block; the 152 block cubes outside the central 4^3 are in the zone of all
-// 8 children. One workgroup per parent runs the z-slab scheme over those cubes for each half cz
-// of the children (target z window (2 + cz) N_g .. (3 + cz) N_g - 1, the accumulators of one
-// window per pass), then the inverse y transform keeping both children's y windows, then for
-// each existing child the inverse x transform, its mean and its zero-mean gridlet. The other 37
-// cubes of each child's zone are added afterwards, cell by cell.
+// 8 children. One workgroup per parent runs the z-slab scheme over those cubes for both halves cz
+// of the children at once (target z windows (2 + cz) N_g .. (3 + cz) N_g - 1, each with its own
+// accumulators; one after the other at N_g = 6 in FP64, where two do not fit), then for each half
+// the inverse y transform keeping both children's y windows, then for each existing child the
+// inverse x transform, its mean and its zero-mean gridlet. The other 37 cubes of each child's zone
+// are added afterwards, cell by cell. 2^18 Plummer, N_g = 6, FP32: 0.49 ms with the halves one after
+// the other, each with its own x and y transforms, 0.36 ms at once.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NG>
 struct ParentShape {
@@ -732,9 +872,10 @@ struct ParentShape {
 };
 
 template <typename T, int NG>
-__global__ __launch_bounds__(kSlabThreads) void k_m2l_parent(M2LArgs<T> a) {
+__global__ __launch_bounds__(kSlabThreads, (sizeof(T) == 4 || NG <= 4 ? 2 : 1)) void k_m2l_parent(M2LArgs<T> a) {
   using S = SlabShape<T, NG>;
   constexpr int n = S::n, H = S::H, M = S::M, NT = S::NT, D = S::D, PER = S::PER, ENT = S::ENT;
+  constexpr int NW = sizeof(T) == 4 || NG <= 4 ? 2 : 1;  // z windows per pass
   static_assert(ParentShape<T, NG>::fits, "parent buffers exceed the LDS budget");
   static_assert(S::ZB >= NG, "the slab buffer holds the N_g accumulated planes");
   __shared__ int s_src[216];
@@ -752,6 +893,8 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_parent(M2LArgs<T> a) {
     sincospi(2.0 * m / n, &sv, &cv);
     s_tw[m] = {cv, sv};
   }
+  uint32_t goff[PER];
+  green_offsets<T, NG, 0>(goff);
 
   const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, jb = blockIdx.x >> 3;
   const int p_begin = int((int64_t(a.nparents) * xcd) / 8);
@@ -770,70 +913,94 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_parent(M2LArgs<T> a) {
     __syncthreads();
     const T* gtab = a.gxy + size_t(__builtin_amdgcn_readfirstlane(l) - 2) * D * H * H;
 
-    for (int cz = 0; cz < 2; ++cz) {
+    // the children's two z windows, NW at a time from the same x and y transforms
+    for (int cz0 = 0; cz0 < 2; cz0 += NW) {
       // block-uniform: every thread reads the same child ids
-      if (s_kid[4 * cz] < 0 && s_kid[4 * cz + 1] < 0 && s_kid[4 * cz + 2] < 0 &&
-          s_kid[4 * cz + 3] < 0)
-        continue;
-      T pr[PER][NG], pim[PER][NG];
-      slab_sum<T, NG>(a, s_src, slab, gtab, (2 + cz) * NG, s_tw, pr, pim);
+      bool want[NW];
+      bool any = false;
 #pragma unroll
-      for (int r = 0; r < PER; ++r) {
-        const int e = tid + NT * r;
-        if (e < ENT) {
-#pragma unroll
-          for (int zz = 0; zz < NG; ++zz) slab[size_t(zz) * ENT + e] = {pr[r][zz], pim[r][zz]};
-        }
+      for (int w = 0; w < NW; ++w) {
+        const int* kid = s_kid + 4 * (cz0 + w);
+        want[w] = __builtin_amdgcn_readfirstlane(int(kid[0] >= 0 || kid[1] >= 0 || kid[2] >= 0 || kid[3] >= 0));
+        any = any || want[w];
       }
-      __syncthreads();
-      // y^-1: red[Z][Y][kx], Y = 2 N_g + yy for yy < 2 N_g (the windows of cy = 0 and 1)
-      for (int w = tid; w < NG * H; w += NT) {
-        const int kx = w % H, zz = w / H;
-        const cplx<T>* col = slab + size_t(zz) * ENT + kx;
-        cplx<T> in[n], out[n];
+      if (!any) continue;
+      T pr[NW][PER][NG], pim[NW][PER][NG];
 #pragma unroll
-        for (int y = 0; y < n; ++y) in[y] = col[size_t(y) * H];
-        fft<n, +1>(in, out);
+      for (int w = 0; w < NW; ++w)
 #pragma unroll
-        for (int yy = 0; yy < 2 * NG; ++yy) red[(size_t(zz) * 2 * NG + yy) * H + kx] = out[2 * NG + yy];
+        for (int r = 0; r < PER; ++r)
+#pragma unroll
+          for (int zz = 0; zz < NG; ++zz) pr[w][r][zz] = pim[w][r][zz] = T(0);
+      for (int z0 = 0; z0 < S::W; z0 += S::ZB) {
+        forward_slab<T, NG, 0>(a, s_src, slab, z0, s_tw);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+          if (want[w]) accumulate_slab<T, NG, 0>(slab, gtab, (2 + cz0 + w) * NG, z0, goff, pr[w], pim[w]);
+        __syncthreads();
       }
-      __syncthreads();
-      for (int c = 4 * cz; c < 4 * cz + 4; ++c) {
-        const int g = s_kid[c];
-        if (g < 0) continue;  // block-uniform
-        const int cx = c & 1, cy = (c >> 1) & 1;
-        // x^-1 (Hermitian half spectrum) in double: out = sum_k w_k Re(F_k e^{+2 pi i k X / n}),
-        // w_k = 1 at k = 0 and n/2, 2 otherwise; X = (2 + c_x) N_g + xx
-        const int Xt = (2 + cx) * NG;
-        for (int q = tid; q < M; q += NT) {
-          const int xx = q % NG, yy = (q / NG) % NG, zz = q / (NG * NG);
-          const int X = Xt + xx;
-          const cplx<T>* F = red + (size_t(zz) * 2 * NG + cy * NG + yy) * H;
-          double acc = 0.0;
-          int m = 0;
-          for (int k = 0; k < H; ++k) {
-            const cplx<double> f = {double(F[k].re), double(F[k].im)};
-            const cplx<double> w = s_tw[m];
-            const double v = f.re * w.re - f.im * w.im;
-            acc += (k == 0 || k == n / 2) ? v : 2.0 * v;
-            m += X;
-            if (m >= n) m -= n;
+#pragma unroll
+      for (int win = 0; win < NW; ++win) {
+        if (!want[win]) continue;
+        const int cz = cz0 + win;
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+          const int e = tid + NT * r;
+          if (e < ENT) {
+#pragma unroll
+            for (int zz = 0; zz < NG; ++zz) slab[size_t(zz) * ENT + e] = {pr[win][r][zz], pim[win][r][zz]};
           }
-          s_out[q] = acc;
         }
         __syncthreads();
-        double part = 0.0;
-        for (int e = tid; e < M; e += NT) part += s_out[e];
-        part = wave_sum(part);
-        if ((tid & 63) == 0) s_red[tid >> 6] = part;
-        __syncthreads();
-        double mean = 0.0;
+        // y^-1: red[Z][Y][kx], Y = 2 N_g + yy for yy < 2 N_g (the windows of cy = 0 and 1)
+        for (int w = tid; w < NG * H; w += NT) {
+          const int kx = w % H, zz = w / H;
+          const cplx<T>* col = slab + size_t(zz) * ENT + kx;
+          cplx<T> in[n], out[n];
 #pragma unroll
-        for (int w = 0; w < NT / 64; ++w) mean += s_red[w];
-        mean *= 1.0 / M;
-        for (int e = tid; e < M; e += NT) a.local[size_t(g) * M + e] = T(s_out[e] - mean);
-        if (tid == 0) a.m2l_mean[g] = mean;
-        __syncthreads();  // s_out and s_red are reused by the next child
+          for (int y = 0; y < n; ++y) in[y] = col[size_t(y) * H];
+          fft<n, +1>(in, out);
+#pragma unroll
+          for (int yy = 0; yy < 2 * NG; ++yy) red[(size_t(zz) * 2 * NG + yy) * H + kx] = out[2 * NG + yy];
+        }
+        __syncthreads();
+        for (int c = 4 * cz; c < 4 * cz + 4; ++c) {
+          const int g = s_kid[c];
+          if (g < 0) continue;  // block-uniform
+          const int cx = c & 1, cy = (c >> 1) & 1;
+          // x^-1 (Hermitian half spectrum) in double: out = sum_k w_k Re(F_k e^{+2 pi i k X / n}),
+          // w_k = 1 at k = 0 and n/2, 2 otherwise; X = (2 + c_x) N_g + xx
+          const int Xt = (2 + cx) * NG;
+          for (int q = tid; q < M; q += NT) {
+            const int xx = q % NG, yy = (q / NG) % NG, zz = q / (NG * NG);
+            const int X = Xt + xx;
+            const cplx<T>* F = red + (size_t(zz) * 2 * NG + cy * NG + yy) * H;
+            double acc = 0.0;
+            int m = 0;
+            for (int k = 0; k < H; ++k) {
+              const cplx<double> f = {double(F[k].re), double(F[k].im)};
+              const cplx<double> w = s_tw[m];
+              const double v = f.re * w.re - f.im * w.im;
+              acc += (k == 0 || k == n / 2) ? v : 2.0 * v;
+              m += X;
+              if (m >= n) m -= n;
+            }
+            s_out[q] = acc;
+          }
+          __syncthreads();
+          double part = 0.0;
+          for (int e = tid; e < M; e += NT) part += s_out[e];
+          part = wave_sum(part);
+          if ((tid & 63) == 0) s_red[tid >> 6] = part;
+          __syncthreads();
+          double mean = 0.0;
+#pragma unroll
+          for (int w = 0; w < NT / 64; ++w) mean += s_red[w];
+          mean *= 1.0 / M;
+          for (int e = tid; e < M; e += NT) a.local[size_t(g) * M + e] = T(s_out[e] - mean);
+          if (tid == 0) a.m2l_mean[g] = mean;
+          __syncthreads();  // s_out and s_red are reused by the next child
+        }
       }
     }
   }
@@ -851,6 +1018,12 @@ constexpr int m2l_kind() {
     static_assert(M2LShape<T, NG>::lds, "whole-grid stage exceeds the LDS budget");
     return 0;
   }
+}
+
+// Which orders take sibling pairs: N_g = 4 in both precisions and N_g = 6 in FP32.
+template <typename T, int NG>
+constexpr bool pair_kernel() {
+  return NG == 4 || (NG == 6 && sizeof(T) == 4);
 }
 
 // resident workgroups of the z-slab kernel on 256 CUs
@@ -891,11 +1064,42 @@ static void m2l_t(Plan& p, hipStream_t s) {
   if (grid > p.m2l_slots) grid = p.m2l_slots;
   p.m2l_split = m2l_kind<T, NG>() == 1;
   p.m2l_mean_ff = false;
+  constexpr bool strict_built = sizeof(T) == 4 && (NG == 4 || NG == 6);
+  const bool strict = strict_built && p.fp32_strict;
+  if (strict) {
+    a.twff = p.tab.twff.as<float4>();
+    p.m2l_mean_ff = true;
+  }
+  if constexpr (pair_kernel<T, NG>()) {
+    // Sibling pairs where they make at least two rounds of the resident workgroups; below, their
+    // longer items leave the chip short of work (Plummer sets, N_g = 6, FP32, us: 133 split parents
+    // 139 in pairs, 123 one by one; 267: 210, 204; 483: 316, 374. N_g = 4, FP64: 133: 98, 83; 483:
+    // 236, 268).
+    const int nparents = p.cell_pbeg[p.nlevels - 1];
+    if (int64_t(nparents) * 4 >= 2 * int64_t(p.m2l_slots)) {
+      a.nparents = nparents;
+      a.plist = p.cell_plist.as<int>();
+      a.child8 = p.child8.as<int>();
+      if (p.cell_plist.bytes < size_t(nparents) * 4) fail(HPM_ERR_DEVICE, "split-parent list missing");
+      grid = p.m2l_slots;
+      constexpr int NT = SlabShape<T, NG>::NT;
+      if constexpr (strict_built) {
+        if (strict) {
+          if (p.ext) k_m2l_pair<T, NG, 1, true><<<grid, NT, 0, s>>>(a);
+          else k_m2l_pair<T, NG, 0, true><<<grid, NT, 0, s>>>(a);
+          HPM_LAUNCH_CHECK();
+          return;
+        }
+      }
+      if (p.ext) k_m2l_pair<T, NG, 1><<<grid, NT, 0, s>>>(a);
+      else k_m2l_pair<T, NG, 0><<<grid, NT, 0, s>>>(a);
+      HPM_LAUNCH_CHECK();
+      return;
+    }
+  }
   if constexpr (m2l_kind<T, NG>() == 1) {
-    if constexpr (sizeof(T) == 4 && (NG == 4 || NG == 6)) {
-      if (p.fp32_strict) {
-        a.twff = p.tab.twff.as<float4>();
-        p.m2l_mean_ff = true;
+    if constexpr (strict_built) {
+      if (strict) {
         if (p.ext) k_m2l_slab<T, NG, 1, true><<<grid, SlabShape<T, NG, 1>::NT, 0, s>>>(a);
         else k_m2l_slab<T, NG, 0, true><<<grid, SlabShape<T, NG>::NT, 0, s>>>(a);
         HPM_LAUNCH_CHECK();
