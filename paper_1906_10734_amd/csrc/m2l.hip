@@ -179,7 +179,8 @@ __device__ __forceinline__ void xpass_row(const M2LArgs<T>& a, int yr, int zr, c
 // The same half spectrum split over two threads by the parity Q of k (decimation in frequency of
 // the n/2-point transform: its even outputs are the n/4-point transform of z_j + z_{j+n/4}, its odd
 // ones that of (z_j - z_{j+n/4}) e^{-2 pi i j / (n/2)}; X_k needs Z_k and Z_{n/2-k}, both of parity
-// Q). The thread writes X_k for k = Q, Q + 2, ... <= n/2 into row[k].
+// Q). The thread writes X_k for k = Q, Q + 2, ... < n/2 into row[k], and X_{n/2}, which is real as X_0
+// is, into row[0]'s imaginary part.
 template <typename T, int NG, int Q>
 __device__ __forceinline__ void xpass_row_half(const M2LArgs<T>& a, int yr, int zr, const int* s_src,
                                                cplx<T>* row) {
@@ -206,6 +207,7 @@ __device__ __forceinline__ void xpass_row_half(const M2LArgs<T>& a, int yr, int 
     else u[j] = twiddle<j, h, -1>(csub(z0, z1));
   });
   fft<hh, -1>(u, Zq);  // Zq[kk] = Z[2 kk + Q]
+  T x0 = T(0);
   static_for<0, hh + 1>([&](auto kc) {
     constexpr int k = 2 * decltype(kc)::value + Q;
     if constexpr (k <= h) {
@@ -213,9 +215,36 @@ __device__ __forceinline__ void xpass_row_half(const M2LArgs<T>& a, int yr, int 
       const cplx<T> e = {T(0.5) * (zk.re + zc.re), T(0.5) * (zk.im - zc.im)};
       const cplx<T> o = {T(0.5) * (zk.im + zc.im), T(0.5) * (zc.re - zk.re)};
       const cplx<T> wo = twiddle<k, n, -1>(o);
-      row[k] = {e.re + wo.re, e.im + wo.im};
+      if constexpr (k == 0) x0 = e.re + wo.re;
+      else if constexpr (k == h) row[0] = {x0, e.re + wo.re};
+      else row[k] = {e.re + wo.re, e.im + wo.im};
     }
   });
+}
+
+// A quarter of a forward y line (decimation in frequency): thread Q of the line's four transforms
+//   u_j = e^{-2 pi i Q j / n} sum_r x_{j + r m} (-i)^{Q r},  j < m = n / 4, rows j + r m < W nonzero,
+// whose m-point transform is the line's outputs ky = 4 k + Q.
+template <typename T, int n, int W, int H, int Q>
+__device__ __forceinline__ void ypass_quarter(const cplx<T>* col, cplx<T> (&out)[n / 4]) {
+  constexpr int m = n / 4;
+  cplx<T> u[m];
+  static_for<0, m>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    cplx<T> acc = col[j * H];
+    static_for<1, 4>([&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      if constexpr (j + r * m < W) {
+        const cplx<T> v = col[(j + r * m) * H];
+        if constexpr ((Q * r) % 4 == 0) acc = cadd(acc, v);
+        else if constexpr ((Q * r) % 4 == 1) acc = cadd(acc, cplx<T>{v.im, -v.re});
+        else if constexpr ((Q * r) % 4 == 2) acc = csub(acc, v);
+        else acc = cadd(acc, cplx<T>{-v.im, v.re});
+      }
+    });
+    u[j] = twiddle<Q * j, n, -1>(acc);
+  });
+  fft<m, -1>(u, out);
 }
 
 template <typename T, int NG>
@@ -366,14 +395,17 @@ struct SlabShape {
   static constexpr int NT = kSlabThreads;
   // At N_g = 8 the inverse y transform is a pruned direct sum in double (FP32 rounding of the
   // inverse transforms would dominate the gradient of a degree-7 interpolant), and its output
-  // buffer in double leaves room for half a block layer per slab. FP64 at N_g = 8 also cannot
-  // hold the accumulators of all N_g target planes (288 registers per thread): it streams two
-  // source rows per slab, forms the target planes in two passes of N_g / 2, and splits each x
-  // line over two threads and each forward y line over four.
+  // buffer in double leaves room for half a block layer per slab. FP64 at N_g = 8 streams two
+  // source rows per slab. Its accumulators take 288 registers of a thread (one workgroup per CU), so
+  // each x line is split over two threads and each forward y line over four, by wave: the waves of a
+  // half or quarter run one code path with immediate twiddles. 2^16 Plummer, N_g = 8: 3.76 ms; 6.03
+  // with the halves and quarters of a line in neighbouring lanes (every path run by every wave) and
+  // 66 columns on 64 lanes (two rounds); 9.33 with four target planes per pass besides, each pass
+  // with its own x and y transforms.
   static constexpr bool wide = NG >= 8;
   static constexpr bool narrow = wide && sizeof(T) == 8;
   static constexpr int ZB = wide ? (narrow ? 2 : NG / 2) : kSlabLayers * NG;  // source rows per slab
-  static constexpr int ZW = narrow ? NG / 2 : NL;           // target z planes per pass
+  static constexpr int ZW = NL;                             // target z planes per pass
   static constexpr int YS = narrow ? 4 : 1;                 // threads per forward y line
   static constexpr int XS = narrow ? 2 : 1;                 // threads per x line
   static constexpr int ZG = ZB < ZW ? ZB : ZW;              // planes per inverse-y group
@@ -408,12 +440,12 @@ __device__ __forceinline__ void forward_slab(const M2LArgs<T>& a, const int* s_s
       for (int k = 0; k < H; ++k) row[k] = X[k];
     }
   } else {
-    // x: two threads per row, one per parity of the output frequency
-    for (int w = tid; w < ZB * W * 2; w += NT) {
-      const int q = w & 1, r = w >> 1;
-      const int zb = r / W, yr = r % W;
+    // x: two threads per row, one per parity of the output frequency, by halves of the workgroup
+    static_assert(ZB * W <= NT / 2, "x split");
+    const int r = tid % (NT / 2), zb = r / W, yr = r % W;
+    if (r < ZB * W) {
       cplx<T>* row = slab + (size_t(zb) * n + yr) * H;
-      if (q == 0) xpass_row_half<T, NG, 0>(a, yr, z0 + zb, s_src, row);
+      if (tid < NT / 2) xpass_row_half<T, NG, 0>(a, yr, z0 + zb, s_src, row);
       else xpass_row_half<T, NG, 1>(a, yr, z0 + zb, s_src, row);
     }
   }
@@ -431,47 +463,34 @@ __device__ __forceinline__ void forward_slab(const M2LArgs<T>& a, const int* s_s
       for (int y = 0; y < n; ++y) col[size_t(y) * H] = out[y];
     }
   } else {
-    // y split over YS threads per column (decimation in frequency): thread q transforms
-    //   u_j = e^{-2 pi i q j / n} sum_r x_{j + r m} e^{-2 pi i q r / YS},  j < m = n / YS,
-    // whose m-point transform is the column's outputs ky = YS k + q. All threads read their
-    // inputs before any output is written back in place.
-    static_assert(YS == 4, "forward y split");
-    constexpr int m = n / YS, TASKS = ZB * H * YS;
-    for (int w0 = 0; w0 < TASKS; w0 += NT) {
-      const int w = w0 + tid;
-      const bool live = w < TASKS;
-      const int q = w % YS, c = w / YS;
-      const int kx = c % H, zb = c / H;
-      cplx<T>* col = slab + size_t(zb) * n * H + kx;
-      cplx<T> u[m], out[m];
-      if (live) {
+    // y split over four threads per column, one wave per quarter; column 0 carries the real columns
+    // kx = 0 and kx = n/2, so a slab is 64 columns. All threads read their inputs before any output
+    // is written back in place.
+    static_assert(YS == 4 && NT == 256 && ZB * (H - 1) == 64, "forward y split");
+    const int lane = tid & 63, q = __builtin_amdgcn_readfirstlane(tid >> 6);
+    cplx<T>* col = slab + size_t(lane / (H - 1)) * n * H + lane % (H - 1);
+    cplx<T> out[n / 4];
+    if (q == 0) ypass_quarter<T, n, W, H, 0>(col, out);
+    else if (q == 1) ypass_quarter<T, n, W, H, 1>(col, out);
+    else if (q == 2) ypass_quarter<T, n, W, H, 2>(col, out);
+    else ypass_quarter<T, n, W, H, 3>(col, out);
+    __syncthreads();
 #pragma unroll
-        for (int j = 0; j < m; ++j) {
-          cplx<T> acc = {T(0), T(0)};
-#pragma unroll
-          for (int r = 0; r < YS; ++r) {
-            if (j + r * m < W) {
-              const cplx<T> v = col[size_t(j + r * m) * H];
-              // times (-i)^(q r)
-              switch ((q * r) & 3) {
-                case 0: acc = cadd(acc, v); break;
-                case 1: acc = cadd(acc, cplx<T>{v.im, -v.re}); break;
-                case 2: acc = csub(acc, v); break;
-                default: acc = cadd(acc, cplx<T>{-v.im, v.re}); break;
-              }
-            }
-          }
-          const cplx<double> t = tw[(q * j) % n];
-          u[j] = cmul(acc, cplx<T>{T(t.re), T(-t.im)});
-        }
-        fft<m, -1>(u, out);
+    for (int k = 0; k < n / 4; ++k) col[size_t(4 * k + q) * H] = out[k];
+    __syncthreads();
+    // the two real columns apart: C = F_0 + i F_{n/2}, F(n - ky) = conj F(ky) for both
+    if (tid < ZB * (n / 2 + 1)) {
+      const int zb = tid / (n / 2 + 1), ky = tid % (n / 2 + 1), kc = (n - ky) % n;
+      cplx<T>* c0 = slab + size_t(zb) * n * H;
+      const cplx<T> u = c0[ky * H], v = c0[kc * H];
+      const cplx<T> f0 = {T(0.5) * (u.re + v.re), T(0.5) * (u.im - v.im)};
+      const cplx<T> f1 = {T(0.5) * (u.im + v.im), T(0.5) * (v.re - u.re)};
+      c0[ky * H] = f0;
+      c0[ky * H + H - 1] = f1;
+      if (kc != ky) {
+        c0[kc * H] = {f0.re, -f0.im};
+        c0[kc * H + H - 1] = {f1.re, -f1.im};
       }
-      __syncthreads();
-      if (live) {
-#pragma unroll
-        for (int k = 0; k < m; ++k) col[size_t(YS * k + q) * H] = out[k];
-      }
-      __syncthreads();
     }
   }
   __syncthreads();
