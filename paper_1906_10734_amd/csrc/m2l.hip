@@ -741,8 +741,7 @@ __device__ __forceinline__ void load_inverse_twiddles(const M2LArgs<T>& a, cplx<
   }
 }
 
-// One target at a time: small trees, and N_g = 8 and FP64 N_g = 6, where a second child's accumulators
-// do not fit.
+// One target at a time: small trees, N_g = 8, and extended gridlets at N_g = 6 in FP64.
 template <typename T, int NG, int EXT, bool STRICT = false>
 __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
   using S = SlabShape<T, NG, EXT>;
@@ -797,11 +796,11 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
 // transforms of a layer for two targets instead of 12. What each target gets is, operation for
 // operation, what it would get alone: its layers' transforms in order, its own z sum and inverse.
 // The transforms are two thirds of the vector instructions that bound the kernel. 2^18 Plummer, N_g =
-// 6, FP32: 1.59 -> 1.28 ms against one target at a time. Two workgroups per CU, as alone, although the
+// 6: FP32 1.59 -> 1.28 ms, FP64 3.39 -> 2.70 ms against one target at a time. Two workgroups per CU, as alone, although the
 // second accumulators then spill up to 40 registers of a thread (N_g = 4, FP64, 483 parents: 236 us, with
 // one workgroup per CU and no spills 322 us); with the extended gridlet at N_g = 6 one fits.
 template <typename T, int NG, int EXT, bool STRICT = false>
-__global__ __launch_bounds__(kSlabThreads, (NG == 6 && EXT ? 1 : 2)) void k_m2l_pair(M2LArgs<T> a) {
+__global__ __launch_bounds__(kSlabThreads, (NG == 6 && (EXT || sizeof(T) == 8) ? 1 : 2)) void k_m2l_pair(M2LArgs<T> a) {
   using S = SlabShape<T, NG, EXT>;
   constexpr int n = S::n, H = S::H, NT = S::NT, D = S::D, PER = S::PER, ZW = S::ZW, NL = S::NL, ML = S::ML;
   static_assert(S::fits, "slab buffers exceed the LDS budget");
@@ -876,7 +875,7 @@ __global__ __launch_bounds__(kSlabThreads, (NG == 6 && EXT ? 1 : 2)) void k_m2l_
 // in the parent's 6^3 block; the 152 block cubes outside the central 4^3 are in the zone of all
 // 8 children. One workgroup per parent runs the z-slab scheme over those cubes for both halves cz
 // of the children at once (target z windows (2 + cz) N_g .. (3 + cz) N_g - 1, each with its own
-// accumulators; one after the other at N_g = 6 in FP64, where two do not fit), then for each half
+// accumulators), then for each half
 // the inverse y transform keeping both children's y windows, then for each existing child the
 // inverse x transform, its mean and its zero-mean gridlet. The other 37 cubes of each child's zone
 // are added afterwards, cell by cell. 2^18 Plummer, N_g = 6, FP32: 0.49 ms with the halves one after
@@ -894,7 +893,7 @@ template <typename T, int NG>
 __global__ __launch_bounds__(kSlabThreads, (sizeof(T) == 4 || NG <= 4 ? 2 : 1)) void k_m2l_parent(M2LArgs<T> a) {
   using S = SlabShape<T, NG>;
   constexpr int n = S::n, H = S::H, M = S::M, NT = S::NT, D = S::D, PER = S::PER, ENT = S::ENT;
-  constexpr int NW = sizeof(T) == 4 || NG <= 4 ? 2 : 1;  // z windows per pass
+  constexpr int NW = 2;  // z windows per pass
   static_assert(ParentShape<T, NG>::fits, "parent buffers exceed the LDS budget");
   static_assert(S::ZB >= NG, "the slab buffer holds the N_g accumulated planes");
   __shared__ int s_src[216];
@@ -1039,10 +1038,13 @@ constexpr int m2l_kind() {
   }
 }
 
-// Which orders take sibling pairs: N_g = 4 in both precisions and N_g = 6 in FP32.
+// Which orders take sibling pairs: N_g = 4 and 6, in FP64 at N_g = 6 the standard gridlet only (with the
+// extended one the spilled accumulators cost what the shared transforms save: 2^18 Plummer, whole
+// evaluation 4.47 ms in pairs, 4.48 ms one by one; 267 parents 0.87, 0.82). At N_g = 8 a second child's
+// accumulators do not fit.
 template <typename T, int NG>
-constexpr bool pair_kernel() {
-  return NG == 4 || (NG == 6 && sizeof(T) == 4);
+constexpr bool pair_kernel(int ext) {
+  return NG == 4 || (NG == 6 && (sizeof(T) == 4 || !ext));
 }
 
 // resident workgroups of the z-slab kernel on 256 CUs
@@ -1089,13 +1091,13 @@ static void m2l_t(Plan& p, hipStream_t s) {
     a.twff = p.tab.twff.as<float4>();
     p.m2l_mean_ff = true;
   }
-  if constexpr (pair_kernel<T, NG>()) {
+  if constexpr (pair_kernel<T, NG>(0)) {
     // Sibling pairs where they make at least two rounds of the resident workgroups; below, their
     // longer items leave the chip short of work (Plummer sets, N_g = 6, FP32, us: 133 split parents
     // 139 in pairs, 123 one by one; 267: 210, 204; 483: 316, 374. N_g = 4, FP64: 133: 98, 83; 483:
     // 236, 268).
     const int nparents = p.cell_pbeg[p.nlevels - 1];
-    if (int64_t(nparents) * 4 >= 2 * int64_t(p.m2l_slots)) {
+    if (pair_kernel<T, NG>(p.ext) && int64_t(nparents) * 4 >= 2 * int64_t(p.m2l_slots)) {
       a.nparents = nparents;
       a.plist = p.cell_plist.as<int>();
       a.child8 = p.child8.as<int>();
@@ -1110,8 +1112,14 @@ static void m2l_t(Plan& p, hipStream_t s) {
           return;
         }
       }
-      if (p.ext) k_m2l_pair<T, NG, 1><<<grid, NT, 0, s>>>(a);
-      else k_m2l_pair<T, NG, 0><<<grid, NT, 0, s>>>(a);
+      if constexpr (pair_kernel<T, NG>(1)) {
+        if (p.ext) {
+          k_m2l_pair<T, NG, 1><<<grid, NT, 0, s>>>(a);
+          HPM_LAUNCH_CHECK();
+          return;
+        }
+      }
+      k_m2l_pair<T, NG, 0><<<grid, NT, 0, s>>>(a);
       HPM_LAUNCH_CHECK();
       return;
     }
