@@ -115,8 +115,8 @@ static size_t projected_bytes(const Plan& p) {
                  need(p.partial, items * 64 * 5 * e) + need(p.p2m_list, rows * 4) +
                  need(p.p2m_level, rows * 4) + need(p.blocks, parents * 216 * 4) +
                  need(p.vlevel, nv * 4) + need(p.vlist, nv * 4);
-  if (int64_t(cells + nv) > p.cap_cells)  // the cell arrays grow for the virtual cubes
-    extra += size_t(int64_t(cells + nv) - p.cap_cells) * (6 + 8 + 27) * 4;
+  if (int64_t(cells + nv) > p.cap_ids)  // coordinates and particle ranges of the virtual cubes
+    extra += size_t(int64_t(cells + nv) - p.cap_ids) * 3 * 4;
   if (p.prob.m2l_mode != HPM_M2L_GRID && p.nlevels > 2) {
     const size_t spec = cell_modes(p.ng, p.ext) * 2 * e;
     const size_t ntg = cells - size_t(p.level_off[2]);
@@ -125,11 +125,21 @@ static size_t projected_bytes(const Plan& p) {
   return p.device_bytes() + extra;
 }
 
+// particles from which the near zone of an execution runs beside the source-to-target step
+constexpr int64_t kForkMinParticles = int64_t(1) << 16;
+
 void rebuild_plan(Plan& p, int64_t n, const void* x, const void* y, const void* z, hipStream_t s) {
   p.valid = false;
   drain_tree(p);
   if (p.timing) HPM_HIP(hipEventRecord(p.tree_ev[0], s));
   p.n = n;
+  // A plan that stays small never forks: no stream or event is made for it, about 60 us of a
+  // one-off solve (stream and events created, waited for and destroyed).
+  if (!p.noalloc && n >= kForkMinParticles && !p.side) {
+    if (!p.fork_ev) HPM_HIP(hipEventCreateWithFlags(&p.fork_ev, hipEventDisableTiming));
+    if (!p.join_ev) HPM_HIP(hipEventCreateWithFlags(&p.join_ev, hipEventDisableTiming));
+    HPM_HIP(hipStreamCreateWithFlags(&p.side, hipStreamNonBlocking));
+  }
   build_tree(p, x, y, z, s);
   if (p.byte_cap) {
     const size_t want = projected_bytes(p);
@@ -179,9 +189,6 @@ void create_plan(Plan& p, const hpm_problem* pr, int64_t n, const void* x, const
     HPM_HIP(hipHostMalloc(reinterpret_cast<void**>(&p.hbox), Plan::kBoxWords * sizeof(int),
                           hipHostMallocMapped | hipHostMallocCoherent));
     HPM_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&p.dbox), p.hbox, 0));
-    HPM_HIP(hipStreamCreateWithFlags(&p.side, hipStreamNonBlocking));
-    HPM_HIP(hipEventCreateWithFlags(&p.fork_ev, hipEventDisableTiming));
-    HPM_HIP(hipEventCreateWithFlags(&p.join_ev, hipEventDisableTiming));
   }
   const int depth = pr->uniform_depth > 0 ? pr->uniform_depth : pr->max_depth;
   build_tables(p, depth + 1, s);
@@ -206,9 +213,6 @@ static void drain_one(Plan& p) {
   p.n_exec += 1;
   p.ring_count -= 1;
 }
-
-// particles from which the near zone of an execution runs beside the source-to-target step
-constexpr int64_t kForkMinParticles = int64_t(1) << 16;
 
 void execute_plan(Plan& p, const void* m, void* phi, void* ax, void* ay, void* az,
                   hipStream_t s) {

@@ -109,18 +109,6 @@ struct DevBuf {
     p = take(b, &in_arena);
     bytes = b;
   }
-  // grow to at least b bytes, preserving the first "keep" bytes
-  void grow(size_t b, size_t keep, hipStream_t s) {
-    if (b <= bytes && p) return;
-    bool qa = false;
-    void* q = take(b, &qa);
-    if (p && keep) HPM_HIP(hipMemcpyAsync(q, p, keep, hipMemcpyDeviceToDevice, s));
-    HPM_HIP(hipStreamSynchronize(s));
-    release();
-    p = q;
-    bytes = b;
-    in_arena = qa;
-  }
   template <typename U>
   U* as() const { return static_cast<U*>(p); }
   void swap(DevBuf& o) {
@@ -170,6 +158,7 @@ struct Plan {
   int level_off[kMaxLevelsHost + 1] = {0};
   int64_t ncells = 0;
   int64_t cap_cells = 0;
+  int64_t cap_ids = 0;  // of ccoord, cpb and cpe: cells and, after them, virtual cubes
   int64_t nleaves = 0;
   int64_t nleaves_lt2 = 0;  // leaves at levels 0 and 1 come first in the leaf list
   size_t elem = 4;          // sizeof(real)
@@ -253,7 +242,8 @@ struct Plan {
   size_t byte_cap = 0;
   int hbox_store[kBoxWords] = {0};
   // a second stream (default priority) on which the near-zone sums run beside the far-field
-  // chain of an execution, with the events that fork it from and join it to the caller's stream
+  // chain of an execution, with the events that fork it from and join it to the caller's stream;
+  // made by the first build with particles enough to use them
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool overlap = true;  // run the near zone on "side" (from kForkMinParticles particles on)

@@ -793,19 +793,42 @@ __global__ __launch_bounds__(256) void k_tree_link(TreeArgs a) {
   }
 }
 
-static void ensure_cells(Plan& p, int64_t need, int64_t keep, hipStream_t s) {
+// (re)allocates the cell arrays for "need" cells, contents lost and no wait for the stream (a wait
+// per array behind the sort, and another per array when virtual cubes were added, made a one-off
+// solve of 4 k particles 664 us; 498 us without them and without the unused side stream). The three arrays that also hold
+// the virtual cubes get "ids" elements or more.
+static void ensure_cells(Plan& p, int64_t need, int64_t ids) {
   if (need <= p.cap_cells) return;
-  int64_t cap = std::max<int64_t>(need, p.cap_cells + p.cap_cells / 2);
-  const size_t c4 = size_t(cap) * 4, k4 = size_t(keep) * 4;
-  p.ckey.grow(c4, k4, s);
-  p.ccoord.grow(c4, k4, s);
-  p.cpb.grow(c4, k4, s);
-  p.cpe.grow(c4, k4, s);
-  p.cparent.grow(c4, k4, s);
-  p.cflags.grow(c4, k4, s);
-  p.child8.grow(c4 * 8, k4 * 8, s);
-  p.nbr27.grow(c4 * 27, k4 * 27, s);
+  const int64_t cap = std::max<int64_t>(need, p.cap_cells + p.cap_cells / 2);
+  const int64_t cap_ids = std::max({cap, ids, p.cap_ids});
+  p.cap_cells = p.cap_ids = 0;  // no capacity to rely on if an allocation below fails
+  const size_t c4 = size_t(cap) * 4, i4 = size_t(cap_ids) * 4;
+  p.ckey.reserve(c4);
+  p.ccoord.reserve(i4);
+  p.cpb.reserve(i4);
+  p.cpe.reserve(i4);
+  p.cparent.reserve(c4);
+  p.cflags.reserve(c4);
+  p.child8.reserve(c4 * 8);
+  p.nbr27.reserve(c4 * 27);
   p.cap_cells = cap;
+  p.cap_ids = cap_ids;
+}
+
+// Room for "need" cells and virtual cubes in the arrays that hold both (coordinates and particle
+// range), the cells kept. Nothing changes if an allocation or copy fails.
+static void ensure_ids(Plan& p, int64_t need, hipStream_t s) {
+  if (need <= p.cap_ids) return;
+  const int64_t cap = std::max<int64_t>(need, p.cap_ids + p.cap_ids / 2);
+  DevBuf grown[3];
+  DevBuf* held[3] = {&p.ccoord, &p.cpb, &p.cpe};
+  for (int k = 0; k < 3; ++k) {
+    grown[k].reserve(size_t(cap) * 4);
+    HPM_HIP(hipMemcpyAsync(grown[k].p, held[k]->p, size_t(p.ncells) * 4, hipMemcpyDeviceToDevice, s));
+  }
+  HPM_HIP(hipStreamSynchronize(s));
+  for (int k = 0; k < 3; ++k) held[k]->swap(grown[k]);
+  p.cap_ids = cap;
 }
 
 // (re)allocates b and clears it when the allocation changes; true if it did
@@ -900,7 +923,9 @@ void build_tree(Plan& p, const void* x, const void* y, const void* z, hipStream_
   } else {
     est = std::max<int64_t>(1024, 6 * int64_t(n) / std::max(1, pr.leaf_capacity) + 64);
   }
-  ensure_cells(p, est, 0, s);
+  // an adaptive tree usually has fewer virtual cubes than cells: room for both at once spares the
+  // first build three allocations, copies and a wait; a plan held to a number of bytes grows later
+  ensure_cells(p, est, uniform || p.noalloc || p.byte_cap ? est : 2 * est);
 
   TreeArgs a;
   a.keys = p.keys.as<uint32_t>();
@@ -964,7 +989,7 @@ void build_tree(Plan& p, const void* x, const void* y, const void* z, hipStream_
     if (total <= p.cap_cells) break;
     if (attempt > 0) fail(HPM_ERR_DEVICE, "tree build: cell count changed between launches");
     // every launch after the count returned at once: grow and run them again
-    ensure_cells(p, total + total / 4 + 64, 0, s);
+    ensure_cells(p, total + total / 4 + 64, 0);
   }
   // a virtual-cube set that filled up: a larger one, listed again
   while (!uniform && p.hbox[Plan::kBoxVirtFull]) {
@@ -1195,7 +1220,7 @@ void finish_virtual(Plan& p, hipStream_t s) {
   const int nt = p.nlevels > 2 ? p.level_off[p.nlevels - 1] - first : 0;
   const int nv = int(p.nvirt);
   if (nv > 0) {
-    ensure_cells(p, p.ncells + nv, p.ncells, s);
+    ensure_ids(p, p.ncells + nv, s);
     p.vlevel.reserve(size_t(nv) * 4);
     p.vlist.reserve(size_t(nv) * 4);
   }
