@@ -65,6 +65,7 @@ constexpr unsigned long long kRsValue = (1ull << 62) - 1;
 constexpr int kRsSpin = 1 << 14;
 constexpr int kRsLook = 8;
 constexpr int kRsMaxPasses = 4;
+constexpr int kRsBatch = 4;  // rounds ranked at once; every tile size is a multiple
 
 struct SortArgs {
   int n;
@@ -126,21 +127,61 @@ __global__ __launch_bounds__(256) void k_keys(int n, const T* x, const T* y, con
 template <typename T, bool LAST>
 __global__ __launch_bounds__(kRsThreads) void k_sort_pass(SortArgs a) {
   __shared__ int s_tile;
+  constexpr int W = kRsThreads / 64;
   __shared__ int s_cnt[256];
-  __shared__ int run[256];
-  __shared__ int wcnt[kRsThreads / 64][256];
-  __shared__ int s_w[kRsThreads / 64];
+  __shared__ int wcnt[kRsBatch * W][256];
+  __shared__ int s_w[W];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) s_tile = atomicAdd(&a.tile_ctr[a.pass], 1);
   s_cnt[tid] = 0;
   __syncthreads();
   const int tile = s_tile;
   const int base = tile * a.rounds * kRsThreads;
-  for (int r = 0; r < a.rounds; ++r) {
-    const int i = base + r * kRsThreads + tid;
-    if (i < a.n) atomicAdd(&s_cnt[(a.kin[i] >> a.shift) & 255u], 1);
+  const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+  uint32_t key[kRsBatch];
+  int val[kRsBatch], rank[kRsBatch];
+  // A batch of four rounds of 256 items in index order: the items, each one's rank among the equal
+  // digits of its wave and round (from ballots over the lanes), and at wcnt the count of each digit
+  // in every wave of every round.
+  auto batch = [&](int r0) {
+#pragma unroll
+    for (int q = 0; q < kRsBatch; ++q) {
+      const int i = base + (r0 + q) * kRsThreads + tid;
+      key[q] = i < a.n ? a.kin[i] : 0u;
+      val[q] = i < a.n ? a.vin[i] : 0;
+    }
+#pragma unroll
+    for (int w = 0; w < kRsBatch * W; ++w) wcnt[w][tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kRsBatch; ++q) {
+      const bool valid = base + (r0 + q) * kRsThreads + tid < a.n;
+      const uint32_t d = (key[q] >> a.shift) & 255u;
+      uint64_t eq = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t mb = __ballot(valid && bit);
+        eq &= bit ? mb : ~mb;
+      }
+      rank[q] = __popcll(eq & lt);
+      if (valid && rank[q] == 0) wcnt[q * W + wave][d] = __popcll(eq);
+    }
+    __syncthreads();
+  };
+  if (a.rounds == kRsBatch) {  // the whole tile is one batch: its counts are the batch's
+    batch(0);
+    int c = 0;
+#pragma unroll
+    for (int w = 0; w < kRsBatch * W; ++w) c += wcnt[w][tid];
+    s_cnt[tid] = c;
+  } else {
+    for (int r = 0; r < a.rounds; ++r) {
+      const int i = base + r * kRsThreads + tid;
+      if (i < a.n) atomicAdd(&s_cnt[(a.kin[i] >> a.shift) & 255u], 1);
+    }
+    __syncthreads();
   }
-  __syncthreads();
   // thread d: the count of digit d in the tiles before this one
   const unsigned long long own = (unsigned long long)s_cnt[tid];
   unsigned long long* st = a.status + (size_t(a.pass) * a.ntiles) * 256;
@@ -179,54 +220,30 @@ __global__ __launch_bounds__(kRsThreads) void k_sort_pass(SortArgs a) {
   // first output position of digit tid: items of smaller digits, then of earlier tiles
   int tot;
   const int dstart = group_scan<kRsThreads>(a.ghist[a.pass * 256 + tid], s_w, tot);
-  run[tid] = dstart + int(excl);
-  const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-  // items in rounds of 256 in index order; within a round the rank of an item among equal digits
-  // comes from wave ballots (lanes) and a per-digit prefix over the four waves: a stable order
-  for (int r = 0; r < a.rounds; ++r) {
-    const int i = base + r * kRsThreads + tid;
-    const bool valid = i < a.n;
-    uint32_t key = 0;
-    int val = 0;
-    if (valid) {
-      key = a.kin[i];
-      val = a.vin[i];
-    }
-    const uint32_t d = (key >> a.shift) & 255u;
+  int next = dstart + int(excl);  // thread d: the output position of the next item of digit d
+  // batch by batch: thread d turns the counts of its digit into output positions, round by round
+  // and wave by wave, so the order is stable
+  for (int r0 = 0; r0 < a.rounds; r0 += kRsBatch) {
+    if (a.rounds != kRsBatch) batch(r0);
 #pragma unroll
-    for (int w = 0; w < kRsThreads / 64; ++w) wcnt[w][tid] = 0;
-    __syncthreads();
-    uint64_t eq = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t mb = __ballot(valid && bit);
-      eq &= bit ? mb : ~mb;
-    }
-    const int rank = __popcll(eq & lt);
-    if (valid && rank == 0) wcnt[wave][d] = __popcll(eq);
-    __syncthreads();
-    {
-      int acc = run[tid];
-#pragma unroll
-      for (int w = 0; w < kRsThreads / 64; ++w) {
-        const int c = wcnt[w][tid];
-        wcnt[w][tid] = acc;
-        acc += c;
-      }
-      run[tid] = acc;
+    for (int w = 0; w < kRsBatch * W; ++w) {
+      const int c = wcnt[w][tid];
+      wcnt[w][tid] = next;
+      next += c;
     }
     __syncthreads();
-    if (valid) {
-      const int pos = wcnt[wave][d] + rank;
+#pragma unroll
+    for (int q = 0; q < kRsBatch; ++q) {
+      if (base + (r0 + q) * kRsThreads + tid >= a.n) continue;
+      const int pos = wcnt[q * W + wave][(key[q] >> a.shift) & 255u] + rank[q];
       if (pos >= 0 && pos < a.n) {  // always true for consistent counts
-        a.kout[pos] = key;
-        a.vout[pos] = val;
+        a.kout[pos] = key[q];
+        a.vout[pos] = val[q];
         if constexpr (LAST) {
-          if (val >= 0 && val < a.n) {
-            static_cast<T*>(a.xs)[pos] = static_cast<const T*>(a.x)[val];
-            static_cast<T*>(a.ys)[pos] = static_cast<const T*>(a.y)[val];
-            static_cast<T*>(a.zs)[pos] = static_cast<const T*>(a.z)[val];
+          if (val[q] >= 0 && val[q] < a.n) {
+            static_cast<T*>(a.xs)[pos] = static_cast<const T*>(a.x)[val[q]];
+            static_cast<T*>(a.ys)[pos] = static_cast<const T*>(a.y)[val[q]];
+            static_cast<T*>(a.zs)[pos] = static_cast<const T*>(a.z)[val[q]];
           }
         }
       }
