@@ -235,17 +235,32 @@ void execute_plan(Plan& p, const void* m, void* phi, void* ax, void* ay, void* a
   // side stream beside the source-to-target step (which leaves ALU and memory slots idle) and
   // the leaf pass waits for it; small ones keep it in line, where the fork costs more than it hides
   const bool fork = p.overlap && p.n >= kForkMinParticles && p.side;
-  if (fork) {
-    HPM_HIP(hipEventRecord(p.fork_ev, s));
+  auto near_beside = [&] {
     HPM_HIP(hipStreamWaitEvent(p.side, p.fork_ev, 0));
     if (pev) HPM_HIP(hipEventRecord(pev[0], p.side));
     launch_p2p(p, p.side);
     if (pev) HPM_HIP(hipEventRecord(pev[1], p.side));
     HPM_HIP(hipEventRecord(p.join_ev, p.side));
-  }
-  if (p.route == HPM_M2L_CELLS) launch_m2l_cells(p, s);
-  else if (p.route == HPM_M2L_SHARED) launch_m2l_shared(p, s);
+  };
+  if (fork) HPM_HIP(hipEventRecord(p.fork_ev, s));
+  // On the cell and shared routes it starts behind the source spectra and is launched after the
+  // products, whose few large workgroups then find their compute units free: from the start, the
+  // near zone's small ones sat on some of them and the products ran unevenly (cells, N_g = 6, FP64:
+  // 100,003 Plummer particles 867 -> 700 us an evaluation, in line 806; 2^18 1.58 -> 1.45 ms; FP32
+  // 439 -> 406 us and 0.88 -> 0.84; shared, FP64, 2^18 1.88 -> 1.71; equal within 1% from 10^6 FP32
+  // particles on). It keeps the early start on the shared route at N_g = 6 in FP32, where the
+  // per-parent kernel would share the chip with it (0.99 ms, 1.18 late), and for N_g <= 3 in FP64 or
+  // on the shared route, where the near zone is the longer part (66,000 particles, N_g = 2: 244 us,
+  // 259 late).
+  const bool late = p.route == HPM_M2L_CELLS    ? p.prec == HPM_F32 || p.ng > 3
+                    : p.route == HPM_M2L_SHARED ? p.ng > 3 && !(p.prec == HPM_F32 && p.ng == 6)
+                                                : false;
+  const hipEvent_t after_spectra = fork && late ? p.fork_ev : nullptr;
+  if (fork && !late) near_beside();
+  if (p.route == HPM_M2L_CELLS) launch_m2l_cells(p, s, after_spectra);
+  else if (p.route == HPM_M2L_SHARED) launch_m2l_shared(p, s, after_spectra);
   else launch_m2l(p, s);
+  if (fork && late) near_beside();
   if (ev) HPM_HIP(hipEventRecord(ev[3], s));
   for (int l = 2; l < p.nlevels; ++l) launch_l2l(p, l, s);  // level 2: re-centring only
   if (ev) HPM_HIP(hipEventRecord(ev[4], s));

@@ -320,10 +320,11 @@ size_t cell_modes(int ng, int ext);
 // the list of split parents that the cell-by-cell route visits is written by the tree build;
 // read_cell_parents takes its per-level bounds from the mailbox
 void read_cell_parents(Plan& p);
-void launch_m2l_cells(Plan& p, hipStream_t s);
+// fork: an event recorded again once the source spectra are formed (null: none)
+void launch_m2l_cells(Plan& p, hipStream_t s, hipEvent_t fork);
 // the shared-transform route: the central cubes cell by cell, the outer cubes by
 // launch_m2l_parents, both added into each target's (mean, zero-mean gridlet)
-void launch_m2l_shared(Plan& p, hipStream_t s);
+void launch_m2l_shared(Plan& p, hipStream_t s, hipEvent_t fork);
 
 // ---- downsweep.hip -------------------------------------------------------------------------------
 // near-zone ranges, work-item counts and offsets of every leaf (enqueued by the tree build before

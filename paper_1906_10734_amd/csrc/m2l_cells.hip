@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cells_inverse(CellArgs<T> a) {
 // SHARED: the route with the transform shared by siblings (the central cubes here, the outer
 // cubes by the per-parent kernel before the inverse adds to its result)
 template <typename T, int NG, int EXT, bool SHARED = false>
-static void cells_t(Plan& p, hipStream_t s) {
+static void cells_t(Plan& p, hipStream_t s, hipEvent_t fork) {
   using S = CellShape<NG, EXT>;
   p.m2l_split = SHARED || sizeof(T) == 4;
   p.m2l_mean_ff = false;  // this route's means are doubles
@@ -775,6 +775,7 @@ static void cells_t(Plan& p, hipStream_t s) {
   constexpr int PER = cells_per_group<NG, EXT>();
   k_cells_forward<T, NG, EXT><<<a.nsources / PER + 1, kCellThreads, 0, s>>>(a);
   HPM_LAUNCH_CHECK();
+  if (fork) HPM_HIP(hipEventRecord(fork, s));
   TileTable tt{};
   constexpr int TILE = kTileParents<T, SHARED>;
   for (int lp = 1; lp <= kMaxLevelsHost; ++lp) {
@@ -814,41 +815,41 @@ void read_cell_parents(Plan& p) {
 }
 
 template <typename T>
-static void cells_dispatch(Plan& p, hipStream_t s) {
+static void cells_dispatch(Plan& p, hipStream_t s, hipEvent_t fork) {
   switch (p.ng * 2 + p.ext) {
-    case 4: cells_t<T, 2, 0>(p, s); break;
-    case 5: cells_t<T, 2, 1>(p, s); break;
-    case 6: cells_t<T, 3, 0>(p, s); break;
-    case 7: cells_t<T, 3, 1>(p, s); break;
-    case 8: cells_t<T, 4, 0>(p, s); break;
-    case 9: cells_t<T, 4, 1>(p, s); break;
-    case 12: cells_t<T, 6, 0>(p, s); break;
-    case 13: cells_t<T, 6, 1>(p, s); break;
-    case 16: cells_t<T, 8, 0>(p, s); break;
+    case 4: cells_t<T, 2, 0>(p, s, fork); break;
+    case 5: cells_t<T, 2, 1>(p, s, fork); break;
+    case 6: cells_t<T, 3, 0>(p, s, fork); break;
+    case 7: cells_t<T, 3, 1>(p, s, fork); break;
+    case 8: cells_t<T, 4, 0>(p, s, fork); break;
+    case 9: cells_t<T, 4, 1>(p, s, fork); break;
+    case 12: cells_t<T, 6, 0>(p, s, fork); break;
+    case 13: cells_t<T, 6, 1>(p, s, fork); break;
+    case 16: cells_t<T, 8, 0>(p, s, fork); break;
     default: fail(HPM_ERR_UNSUPPORTED, "no cell-by-cell kernels for this gridlet");
   }
 }
 
-void launch_m2l_cells(Plan& p, hipStream_t s) {
-  if (p.prec == HPM_F32) cells_dispatch<float>(p, s);
-  else cells_dispatch<double>(p, s);
+void launch_m2l_cells(Plan& p, hipStream_t s, hipEvent_t fork) {
+  if (p.prec == HPM_F32) cells_dispatch<float>(p, s, fork);
+  else cells_dispatch<double>(p, s, fork);
 }
 
 template <typename T>
-static void shared_dispatch(Plan& p, hipStream_t s) {
+static void shared_dispatch(Plan& p, hipStream_t s, hipEvent_t fork) {
   if (p.ext) fail(HPM_ERR_UNSUPPORTED, "the shared-transform route has no extended gridlet");
   switch (p.ng) {
-    case 2: cells_t<T, 2, 0, true>(p, s); break;
-    case 3: cells_t<T, 3, 0, true>(p, s); break;
-    case 4: cells_t<T, 4, 0, true>(p, s); break;
-    case 6: cells_t<T, 6, 0, true>(p, s); break;
+    case 2: cells_t<T, 2, 0, true>(p, s, fork); break;
+    case 3: cells_t<T, 3, 0, true>(p, s, fork); break;
+    case 4: cells_t<T, 4, 0, true>(p, s, fork); break;
+    case 6: cells_t<T, 6, 0, true>(p, s, fork); break;
     default: fail(HPM_ERR_UNSUPPORTED, "no shared-transform kernels for this gridlet");
   }
 }
 
-void launch_m2l_shared(Plan& p, hipStream_t s) {
-  if (p.prec == HPM_F32) shared_dispatch<float>(p, s);
-  else shared_dispatch<double>(p, s);
+void launch_m2l_shared(Plan& p, hipStream_t s, hipEvent_t fork) {
+  if (p.prec == HPM_F32) shared_dispatch<float>(p, s, fork);
+  else shared_dispatch<double>(p, s, fork);
 }
 
 }  // namespace hpm
