@@ -289,6 +289,42 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// The matrix instructions multiply every slot, the near ones by zero Green values, and zero times an
+// infinite or NaN spectrum (an infinite mass, or one that overflows) is NaN. A child whose result is
+// not finite is therefore summed again over its own zone alone, slot by slot in the same order, so
+// that a source has no part in the far field of the targets near it, as on the padded grid. Only
+// such results come here, behind a test of the finished sums.
+template <typename T, int NG, int EXT, bool CENTRAL>
+__device__ __forceinline__ cplx<T> zone_sum(const CellArgs<T>& a, int lp, int parent, int child, int mode) {
+  using S = CellShape<NG, EXT>;
+  constexpr int B0 = AccumShape<CENTRAL>::B0, NB = AccumShape<CENTRAL>::NB;
+  const int cx = child & 1, cy = (child >> 1) & 1, cz = child >> 2;
+  const int re = mode_pos<T>(mode, 0), im = mode_pos<T>(mode, 1);
+  const T* G = a.gcell + size_t(lp - 1) * S::OFFS * 2 * S::KP;
+  const int* ids = a.blocks + size_t(parent - a.first_parent) * 216;
+  cplx<T> o = {T(0), T(0)};
+#pragma unroll 1
+  for (int s = 0; s < NB * NB * NB; ++s) {
+    const int bx = B0 + s % NB, by = B0 + (s / NB) % NB, bz = B0 + s / (NB * NB);
+    const int dx = bx - 2 - cx, dy = by - 2 - cy, dz = bz - 2 - cz;
+    if (abs(dx) <= 1 && abs(dy) <= 1 && abs(dz) <= 1) continue;
+    const int id = ids[bx + 6 * by + 36 * bz];
+    const T* sv = a.sspec + size_t(id >= 0 ? id - a.first_cell : a.nsources) * 2 * S::KP;
+    const T* gv = G + size_t((dx + 3) + 7 * (dy + 3) + 49 * (dz + 3)) * 2 * S::KP;
+    const T gr = gv[re], gi = gv[im], sr = sv[re], si = sv[im];
+    o.re = fma(gr, sr, o.re);
+    o.re = fma(-gi, si, o.re);
+    o.im = fma(gr, si, o.im);
+    o.im = fma(gi, sr, o.im);
+  }
+  return o;
+}
+
+template <typename T>
+__device__ __forceinline__ bool finite(T x) {
+  return fabs(x) <= (sizeof(T) == 4 ? T(3.402823466e+38) : T(1.7976931348623157e308));
+}
+
 // FP32. v_mfma_f32_4x4x1: 16 blocks (modes) of 4 children times 4 parents, one slot per
 // instruction. Each instruction is one fused multiply-add per result, so a result's terms are added
 // in slot order, real products before cross terms: the FP32 rounding of the sums (which the
@@ -474,6 +510,7 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
     }
     // register r of lane l: child r of the quad, parent l % 4
     if (mp < pieces) {
+      float* out = a.tspec + chunk * 2 * KC + mp * 4;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const int k = wave * WP + p * 4 + i;
@@ -484,9 +521,26 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
           for (int r = 0; r < 4; ++r) {
             const int t = k < pn ? kids[4 * c + r] : -1;
             if (t >= 0)
-              *reinterpret_cast<f4*>(a.tspec + size_t(t - a.first_cell) * 2 * KP + chunk * 2 * KC + mp * 4) =
+              *reinterpret_cast<f4*>(out + size_t(t - a.first_cell) * 2 * KP) =
                   f4{re[0][c][p][r], im[0][c][p][r], re[1][c][p][r], im[1][c][p][r]};
           }
+      }
+      // a source that is not finite shows in either part of every child, near or far: one part of
+      // one child tells (a sum that overflows by itself is what it would be slot by slot)
+      if (!(finite(re[0][0][0][0]) && finite(re[1][0][0][0]) && finite(re[0][0][1][0]) && finite(re[1][0][1][0]))) {
+#pragma unroll 1
+        for (int e = 0; e < 16; ++e) {
+          const int k = wave * WP + (e >> 3) * 4 + i;
+          if (k >= pn) break;
+          const int par = plist[p0 + k], t = a.child8[size_t(par) * 8 + (e & 7)];
+          if (t < 0) continue;
+          f4* at = reinterpret_cast<f4*>(out + size_t(t - a.first_cell) * 2 * KP);
+          const f4 v = *at;
+          if (finite(v[0]) && finite(v[1]) && finite(v[2]) && finite(v[3])) continue;
+          const cplx<float> lo = zone_sum<float, NG, EXT, CENTRAL>(a, lp, par, e & 7, chunk * KC + 2 * mp);
+          const cplx<float> hi = zone_sum<float, NG, EXT, CENTRAL>(a, lp, par, e & 7, chunk * KC + 2 * mp + 1);
+          *at = f4{lo.re, lo.im, hi.re, hi.im};
+        }
       }
     }
   }
@@ -600,7 +654,10 @@ __global__ __launch_bounds__((kAccumThreads<double, CENTRAL>), (kAccumPerCU<doub
     // D(c, Gr), D(c, Gi) of this column's part of S: the real part of T_c is D(Gr) of the real
     // column minus D(Gi) of the imaginary one, the imaginary part the sum of the other two
     const int k = wave * WP + bpar;
-    const int* kids = a.child8 + size_t(plist[p0 + min(k, pn - 1)]) * 8;
+    const int par = plist[p0 + min(k, pn - 1)];
+    const int* kids = a.child8 + size_t(par) * 8;
+    double* out = a.tspec + chunk * 2 * KC + bpart * 2;
+    d2 all = {0.0, 0.0};  // not finite where a value is not (or, harmlessly, the sum)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int t = k < pn ? kids[q + 4 * h] : -1;
@@ -610,9 +667,21 @@ __global__ __launch_bounds__((kAccumThreads<double, CENTRAL>), (kAccumPerCU<doub
         const double x1 = __shfl_xor(acc[2 * w + 1][2 * h + 1], 1, 64);
         const d2 o = bpart ? d2{acc[2 * w][2 * h] + x0, acc[2 * w + 1][2 * h] + x1}
                            : d2{acc[2 * w][2 * h] - x0, acc[2 * w + 1][2 * h] - x1};
-        if (t >= 0)
-          *reinterpret_cast<d2*>(a.tspec + size_t(t - a.first_cell) * 2 * KP + chunk * 2 * KC +
-                                 (2 * w + bpart) * 2) = o;
+        all += o;
+        if (t >= 0) *reinterpret_cast<d2*>(out + size_t(t - a.first_cell) * 2 * KP + 4 * w) = o;
+      }
+    }
+    if (k < pn && !finite(all.x + all.y)) {
+#pragma unroll 1
+      for (int e = 0; e < 8; ++e) {  // (child's half, mode pair)
+        const int child = q + 4 * (e >> 2), w = e & 3, t = kids[child];
+        if (t < 0) continue;
+        d2* at = reinterpret_cast<d2*>(out + size_t(t - a.first_cell) * 2 * KP + 4 * w);
+        const d2 v = *at;
+        if (finite(v.x) && finite(v.y)) continue;
+        const cplx<double> lo = zone_sum<double, NG, EXT, CENTRAL>(a, lp, par, child, chunk * KC + 2 * w);
+        const cplx<double> hi = zone_sum<double, NG, EXT, CENTRAL>(a, lp, par, child, chunk * KC + 2 * w + 1);
+        *at = bpart ? d2{lo.im, hi.im} : d2{lo.re, hi.re};
       }
     }
   }
