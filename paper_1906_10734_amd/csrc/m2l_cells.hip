@@ -210,15 +210,23 @@ __global__ __launch_bounds__(kCellThreads) void k_cells_forward(CellArgs<T> a) {
 // XCD, taken by its workgroups in turn: those in flight share a chunk and neighbouring parents,
 // whose source rows overlap in the XCD's L2.
 // ---------------------------------------------------------------------------------------------
-// threads of a workgroup and its parents, 8 per wave; resident workgroups per CU (two waves per SIMD)
+// threads of a workgroup and its parents, 8 per wave (FINE: 4 per pair of waves, see the FP32 kernel);
+// resident workgroups per CU (two waves per SIMD)
 template <typename T, bool CENTRAL>
 constexpr int kAccumThreads = sizeof(T) == 4 && !CENTRAL ? 512 : 256;
-template <typename T, bool CENTRAL>
-constexpr int kTileParents = kAccumThreads<T, CENTRAL> / 8;
+template <typename T, bool CENTRAL, bool FINE = false>
+constexpr int kTileParents = kAccumThreads<T, CENTRAL> / (FINE ? 32 : 8);
 template <typename T, bool CENTRAL>
 constexpr int kAccumPerCU = 512 / kAccumThreads<T, CENTRAL>;
 template <typename T>
 constexpr int kChunkModes = sizeof(T) == 4 ? 32 : 8;
+
+// FP32: up to this many items, half the CUs, the fine split is the faster one (evaluations of uniform
+// and Plummer sets of 500 to 240,000 particles, us): 8 parents, N_g = 4, 84 -> 63 (one thread per
+// (parent, mode) on the vector ALU: 63); 72 parents, 126 -> 81 (107); 32 parents in 128 items, N_g = 6,
+// 193 -> 174; 584 in 100, 155 -> 143. Above it loses more often than it gains: 4680 in 148, 223 -> 234;
+// 929 in 180, 255 -> 264; 1880 in 1024, 738 -> 880.
+constexpr int kFineItems = 128;
 
 struct TileTable {
   int ntiles;                       // tiles of all parent levels
@@ -333,7 +341,10 @@ __device__ __forceinline__ bool finite(T x) {
 // Lane l holds modes 2 (l / 4) and 2 (l / 4) + 1 of the chunk's 32 and, as an operand, child or parent
 // l % 4 of a quad; 2 x 2 quads of (children, parents) with real and imaginary parts of two modes are
 // 16 accumulators. A step is one slot; loads run one row of slots (fixed by, bz) ahead.
-template <int NG, int EXT, bool CENTRAL = false>
+//
+// FINE: a wave takes one quad of parents and one of children, a quarter of the products per slot, so
+// that a tree with fewer tiles than CUs has a chain of 216 short steps instead of 216 long ones.
+template <int NG, int EXT, bool CENTRAL = false, bool FINE = false>
 __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float, CENTRAL>)) void k_cells_accum_f32(CellArgs<float> a,
                                                                              TileTable tt,
                                                                              const int* plist) {
@@ -342,23 +353,27 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
   typedef float f4 __attribute__((ext_vector_type(4)));
   constexpr int KP = S::KP, KC = kChunkModes<float>, NCH = (KP + KC - 1) / KC;
   constexpr int OW = A::OW, OR = A::OR, NOFF = A::NOFF, B0 = A::B0, NB = A::NB;
-  constexpr int TILE = kTileParents<float, CENTRAL>, WP = 8;  // parents of a tile, of a wave
+  constexpr int NQ = FINE ? 1 : 2;                            // quads of a wave's parents, and of its children
+  constexpr int TILE = kTileParents<float, CENTRAL, FINE>, WP = 4 * NQ;  // parents of a tile, of a wave
   constexpr int PC = KC / 2;                         // 16-byte pieces (mode pairs) of a row
   constexpr int NR = NB * NB;                        // rows of slots
   __shared__ f4 s_g[NOFF * PC];                      // [offset][pieces, swizzled]
-  __shared__ f4 s_b[TILE / WP][2 * WP * PC];         // per wave: [buffer][parent][pieces, swizzled]
+  constexpr int NW = kAccumThreads<float, CENTRAL> / 64;
+  __shared__ f4 s_b[NW][2 * WP * PC];                // per wave: [buffer][parent][pieces, swizzled]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int mp = lane >> 2, i = lane & 3;            // mode pair, child or parent of a quad
   const int cx = i & 1, cy = i >> 1;
-  // byte offsets into s_g of (child i of either cz, this mode pair) at slot (0, 0, 0), for slots
-  // whose bx and by have parities px and py
+  // first child half of the wave, place of its parents in the tile
+  const int cz0 = FINE ? wave & 1 : 0, wp0 = (FINE ? wave >> 1 : wave) * WP;
+  // byte offsets into s_g of (child i of cz = cz0 + 1, this mode pair) at slot (0, 0, 0), for slots whose
+  // bx and by have parities px and py
   int ga[2][2];
 #pragma unroll
   for (int py = 0; py < 2; ++py)
 #pragma unroll
     for (int px = 0; px < 2; ++px) {
       const int swz = ((1 - cx + px) & 1) | (((1 - cy + py) & 1) << 1);
-      ga[py][px] = (((1 - cx) + OW * (1 - cy)) * PC + (mp ^ (swz << 2))) * 16;
+      ga[py][px] = (((1 - cx) + OW * (1 - cy) - OW * OW * cz0) * PC + (mp ^ (swz << 2))) * 16;
     }
   const char* sg = reinterpret_cast<const char*>(s_g);
   const f4* sb = s_b[wave] + i * PC + (mp ^ (i << 2));  // parent i of either quad, this mode pair
@@ -388,11 +403,11 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
       }
       __syncthreads();
     }
-    if (wave * WP >= pn) continue;  // wave-uniform; the barriers above are workgroup-uniform
+    if (wp0 >= pn) continue;  // wave-uniform; the barriers above are workgroup-uniform
     // row ids: lane (parent lane / 8, bx lane % 8) holds one row of slots of its parent (the zero row
     // for an empty slot; any valid table row for an absent parent, whose ids are not used)
-    const int ipar = wave * WP + (lane >> 3);
-    const bool have = ipar < pn;
+    const int ipar = wp0 + (lane >> 3);
+    const bool have = ipar < pn && (lane >> 3) < WP;
     const int* ids = a.blocks + size_t(plist[p0 + min(ipar, pn - 1)] - a.first_parent) * 216 + B0 * 43 +
                      min(lane & 7, NB - 1);
     auto load_ids = [&](int row) {
@@ -400,39 +415,39 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
       return have && v >= 0 ? v - a.first_cell : a.nsources;
     };
     const float* spec = a.sspec + chunk * 2 * KC + (lpiece < pieces ? lpiece : 0) * 4;
-    f4 rows[NB][2];
+    f4 rows[NB][NQ];
     // spectrum rows of slot bx, both of the loader's parents, from a row of ids
-    auto row_of = [&](int idv, int bx, int (&r)[2]) {
+    auto row_of = [&](int idv, int bx, int (&r)[NQ]) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) r[j] = __shfl(idv, (lpar + 4 * j) * 8 + bx, 64);
+      for (int j = 0; j < NQ; ++j) r[j] = __shfl(idv, (lpar + 4 * j) * 8 + bx, 64);
     };
-    auto load_rows = [&](const int (&r)[2], f4 (&to)[2]) {
+    auto load_rows = [&](const int (&r)[NQ], f4 (&to)[NQ]) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) to[j] = *reinterpret_cast<const f4*>(spec + size_t(r[j]) * 2 * KP);
+      for (int j = 0; j < NQ; ++j) to[j] = *reinterpret_cast<const f4*>(spec + size_t(r[j]) * 2 * KP);
     };
-    auto put_rows = [&](int buf, const f4 (&from)[2]) {
+    auto put_rows = [&](int buf, const f4 (&from)[NQ]) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) sw[(buf * WP + 4 * j) * PC] = from[j];
+      for (int j = 0; j < NQ; ++j) sw[(buf * WP + 4 * j) * PC] = from[j];
     };
     // Green values of slot bx of the row at gr (by of parity py), and this lane's two parents' spectra
-    auto load_slot = [&](const char* gr, int py, int bx, f4 (&g)[2], f4 (&v)[2]) {
+    auto load_slot = [&](const char* gr, int py, int bx, f4 (&g)[NQ], f4 (&v)[NQ]) {
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int c = 0; c < NQ; ++c)
         g[c] = *reinterpret_cast<const f4*>(gr + ga[py][bx & 1] + (bx + OW * OW * (1 - c)) * (PC * 16));
 #pragma unroll
-      for (int p = 0; p < 2; ++p) v[p] = sb[((bx & 1) * WP + 4 * p) * PC];
+      for (int p = 0; p < NQ; ++p) v[p] = sb[((bx & 1) * WP + 4 * p) * PC];
     };
     auto mac = [](float x, float y, f4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(x, y, c, 0, 0, 0); };
-    f4 re[2][2][2], im[2][2][2];  // [mode][cz][parent quad]
+    f4 re[2][NQ][NQ], im[2][NQ][NQ];  // [mode][cz - cz0][parent quad]
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int c = 0; c < NQ; ++c)
 #pragma unroll
-        for (int p = 0; p < 2; ++p) re[m][c][p] = im[m][c][p] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < NQ; ++p) re[m][c][p] = im[m][c][p] = f4{0.f, 0.f, 0.f, 0.f};
     // ids of the rows of slots after the current one (past the last: the last one's again)
     int id1 = load_ids(min(1, NR - 1)), id2 = load_ids(min(2, NR - 1));
-    int r[2];
+    int r[NQ];
     {
       const int id0 = load_ids(0);
 #pragma unroll
@@ -450,7 +465,7 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
     row_of(id1, 1, r);
     load_rows(r, rows[1]);
     row_of(id1, 2, r);  // the next load's rows, ready before they are wanted
-    f4 g[2], v[2], gn[2], vn[2];
+    f4 g[NQ], v[NQ], gn[NQ], vn[NQ];
     load_slot(sg, 0, 0, g, v);
     // rows of slots in pairs, by even and odd (NB is even)
     auto green_row = [&](int row) { return sg + (OW * (row % NB) + OW * OW * (row / NB)) * (PC * 16); };
@@ -477,29 +492,34 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
           wave_lds_fence();
           row_of(bx + 3 < N ? id1 : id2, (bx + 3) % N, r);
           __builtin_amdgcn_sched_barrier(0);
-          // two rounds of 16 independent products
+          // two rounds of 16 (FINE: 4) independent products
 #pragma unroll
           for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int c = 0; c < NQ; ++c)
 #pragma unroll
-              for (int p = 0; p < 2; ++p) {
+              for (int p = 0; p < NQ; ++p) {
                 re[m][c][p] = mac(g[c][2 * m], v[p][2 * m], re[m][c][p]);
                 im[m][c][p] = mac(g[c][2 * m], v[p][2 * m + 1], im[m][c][p]);
               }
-          const float ng[2][2] = {{-g[0][1], -g[0][3]}, {-g[1][1], -g[1][3]}};
+          float ng[NQ][2];
+#pragma unroll
+          for (int c = 0; c < NQ; ++c) {
+            ng[c][0] = -g[c][1];
+            ng[c][1] = -g[c][3];
+          }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int c = 0; c < NQ; ++c)
 #pragma unroll
-              for (int p = 0; p < 2; ++p) {
+              for (int p = 0; p < NQ; ++p) {
                 re[m][c][p] = mac(ng[c][m], v[p][2 * m + 1], re[m][c][p]);
                 im[m][c][p] = mac(g[c][2 * m + 1], v[p][2 * m], im[m][c][p]);
               }
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
+          for (int c = 0; c < NQ; ++c) {
             g[c] = gn[c];
             v[c] = vn[c];
           }
@@ -512,14 +532,14 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
     if (mp < pieces) {
       float* out = a.tspec + chunk * 2 * KC + mp * 4;
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int k = wave * WP + p * 4 + i;
+      for (int p = 0; p < NQ; ++p) {
+        const int k = wp0 + p * 4 + i;
         const int* kids = a.child8 + size_t(plist[p0 + min(k, pn - 1)]) * 8;
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < NQ; ++c)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int t = k < pn ? kids[4 * c + r] : -1;
+            const int t = k < pn ? kids[4 * (cz0 + c) + r] : -1;
             if (t >= 0)
               *reinterpret_cast<f4*>(out + size_t(t - a.first_cell) * 2 * KP) =
                   f4{re[0][c][p][r], im[0][c][p][r], re[1][c][p][r], im[1][c][p][r]};
@@ -527,18 +547,21 @@ __global__ __launch_bounds__((kAccumThreads<float, CENTRAL>), (kAccumPerCU<float
       }
       // a source that is not finite shows in either part of every child, near or far: one part of
       // one child tells (a sum that overflows by itself is what it would be slot by slot)
-      if (!(finite(re[0][0][0][0]) && finite(re[1][0][0][0]) && finite(re[0][0][1][0]) && finite(re[1][0][1][0]))) {
+      bool odd = false;
+#pragma unroll
+      for (int p = 0; p < NQ; ++p) odd = odd || !finite(re[0][0][p][0]) || !finite(re[1][0][p][0]);
+      if (odd) {
 #pragma unroll 1
-        for (int e = 0; e < 16; ++e) {
-          const int k = wave * WP + (e >> 3) * 4 + i;
+        for (int e = 0; e < 4 * NQ * NQ; ++e) {
+          const int k = wp0 + e / (4 * NQ) * 4 + i, child = 4 * cz0 + e % (4 * NQ);
           if (k >= pn) break;
-          const int par = plist[p0 + k], t = a.child8[size_t(par) * 8 + (e & 7)];
+          const int par = plist[p0 + k], t = a.child8[size_t(par) * 8 + child];
           if (t < 0) continue;
           f4* at = reinterpret_cast<f4*>(out + size_t(t - a.first_cell) * 2 * KP);
           const f4 v = *at;
           if (finite(v[0]) && finite(v[1]) && finite(v[2]) && finite(v[3])) continue;
-          const cplx<float> lo = zone_sum<float, NG, EXT, CENTRAL>(a, lp, par, e & 7, chunk * KC + 2 * mp);
-          const cplx<float> hi = zone_sum<float, NG, EXT, CENTRAL>(a, lp, par, e & 7, chunk * KC + 2 * mp + 1);
+          const cplx<float> lo = zone_sum<float, NG, EXT, CENTRAL>(a, lp, par, child, chunk * KC + 2 * mp);
+          const cplx<float> hi = zone_sum<float, NG, EXT, CENTRAL>(a, lp, par, child, chunk * KC + 2 * mp + 1);
           *at = f4{lo.re, lo.im, hi.re, hi.im};
         }
       }
@@ -813,6 +836,18 @@ __global__ __launch_bounds__(kCellThreads) void k_cells_inverse(CellArgs<T> a) {
   }
 }
 
+// tiles of at most "tile" split parents of one level
+static TileTable tile_table(const Plan& p, int tile) {
+  TileTable tt{};
+  for (int lp = 1; lp <= kMaxLevelsHost; ++lp) {
+    tt.first[lp] = tt.ntiles;
+    tt.pbeg[lp] = p.cell_pbeg[std::min(lp, p.nlevels - 1)];
+    if (lp + 1 < p.nlevels)
+      tt.ntiles += (p.cell_pbeg[lp + 1] - p.cell_pbeg[lp] + tile - 1) / tile;
+  }
+  return tt;
+}
+
 // SHARED: the route with the transform shared by siblings (the central cubes here, the outer
 // cubes by the per-parent kernel before the inverse adds to its result)
 template <typename T, int NG, int EXT, bool SHARED = false>
@@ -845,22 +880,20 @@ static void cells_t(Plan& p, hipStream_t s, hipEvent_t fork) {
   k_cells_forward<T, NG, EXT><<<a.nsources / PER + 1, kCellThreads, 0, s>>>(a);
   HPM_LAUNCH_CHECK();
   if (fork) HPM_HIP(hipEventRecord(fork, s));
-  TileTable tt{};
-  constexpr int TILE = kTileParents<T, SHARED>;
-  for (int lp = 1; lp <= kMaxLevelsHost; ++lp) {
-    tt.first[lp] = tt.ntiles;
-    tt.pbeg[lp] = p.cell_pbeg[std::min(lp, p.nlevels - 1)];
-    if (lp + 1 < p.nlevels)
-      tt.ntiles += (p.cell_pbeg[lp + 1] - p.cell_pbeg[lp] + TILE - 1) / TILE;
-  }
+  constexpr int64_t chunks = (S::KP + kChunkModes<T> - 1) / kChunkModes<T>;
+  TileTable tt = tile_table(p, kTileParents<T, SHARED>);
+  const bool fine = sizeof(T) == 4 && chunks * tt.ntiles <= kFineItems;
+  if (fine) tt = tile_table(p, kTileParents<T, SHARED, sizeof(T) == 4>);
   if (tt.ntiles > 0) {
-    constexpr int64_t chunks = (S::KP + kChunkModes<T> - 1) / kChunkModes<T>;
     const int64_t items = chunks * tt.ntiles;
     if (items > (int64_t(1) << 30)) fail(HPM_ERR_UNSUPPORTED, "too many cells for the cell-by-cell route");
     const int grid = int(std::min<int64_t>((items + 7) / 8 * 8, 256 * kAccumPerCU<T, SHARED>));
-    if constexpr (sizeof(T) == 4)
-      k_cells_accum_f32<NG, EXT, SHARED><<<grid, kAccumThreads<T, SHARED>, 0, s>>>(a, tt, p.cell_plist.as<int>());
-    else
+    if constexpr (sizeof(T) == 4) {
+      if (fine)
+        k_cells_accum_f32<NG, EXT, SHARED, true><<<grid, kAccumThreads<T, SHARED>, 0, s>>>(a, tt, p.cell_plist.as<int>());
+      else
+        k_cells_accum_f32<NG, EXT, SHARED><<<grid, kAccumThreads<T, SHARED>, 0, s>>>(a, tt, p.cell_plist.as<int>());
+    } else
       k_cells_accum_f64<NG, EXT, SHARED><<<grid, kAccumThreads<T, SHARED>, 0, s>>>(a, tt, p.cell_plist.as<int>());
     HPM_LAUNCH_CHECK();
   }
