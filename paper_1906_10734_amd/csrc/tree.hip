@@ -861,17 +861,10 @@ static bool reserve_cleared(DevBuf& b, size_t bytes, hipStream_t s) {
   return true;
 }
 
-// Cells the hash tables are sized for: the arrays' capacity, or the cells and virtual cubes of the
-// last build where those are more (2^18 Plummer particles: 2^17 slots instead of 2^16, cell inserts
-// 7.0 instead of 9.4 us and cube inserts 30.5 instead of 33.2 us)
-static int64_t hashed_cells(const Plan& p) {
-  return std::max<int64_t>(p.cap_cells, p.ncells + p.nvirt);
-}
-
 // the cube hash (at least twice as many slots as cells)
 static void reserve_cube_hash(Plan& p, hipStream_t s) {
   int bits = 12;
-  while ((int64_t(1) << bits) < 2 * hashed_cells(p) && bits < 31) ++bits;
+  while ((int64_t(1) << bits) < 2 * p.sized_cells() && bits < 31) ++bits;
   if (bits > p.chash_bits || !p.chash_slot.p) {
     p.chash_bits = std::max(bits, p.chash_bits);
     const size_t slots = size_t(1) << p.chash_bits;
@@ -1227,7 +1220,7 @@ static VirtArgs virt_args(Plan& p) {
 // when it is (re)allocated
 static void reserve_virt_set(Plan& p, int min_bits, hipStream_t s) {
   int bits = std::max(13, min_bits);
-  while ((int64_t(1) << bits) < 4 * hashed_cells(p) && bits < 30) ++bits;
+  while ((int64_t(1) << bits) < 4 * p.sized_cells() && bits < 30) ++bits;
   if (bits <= p.vhash_bits && p.vhash_keys.p) return;
   p.vhash_bits = bits;
   const size_t slots = size_t(1) << bits;
