@@ -838,10 +838,14 @@ static void ensure_cells(Plan& p, int64_t need, int64_t ids) {
 }
 
 // Room for "need" cells and virtual cubes in the arrays that hold both (coordinates and particle
-// range), the cells kept. Nothing changes if an allocation or copy fails.
+// range), the cells kept. Nothing of them changes if an allocation or copy fails. A plan held to a
+// number of bytes takes just the room it was checked for, and gives its gridlets up first (their
+// rows follow the same count and are allocated again right after), so that the old and new arrays
+// together stay within what it will hold.
 static void ensure_ids(Plan& p, int64_t need, hipStream_t s) {
   if (need <= p.cap_ids) return;
-  const int64_t cap = std::max<int64_t>(need, p.cap_ids + p.cap_ids / 2);
+  const int64_t cap = p.byte_cap ? need : std::max<int64_t>(need, p.cap_ids + p.cap_ids / 2);
+  if (p.byte_cap) p.gridlet.release();
   DevBuf grown[3];
   DevBuf* held[3] = {&p.ccoord, &p.cpb, &p.cpe};
   for (int k = 0; k < 3; ++k) {
