@@ -326,6 +326,8 @@ int m2l_workspace_slots(int prec, int ng, size_t* bytes_per_slot);
 // modes of one cell spectrum as stored: C^2 (C/2 + 1) with C = 2 N_g + 2 ext, rounded up to a
 // multiple of 16
 size_t cell_modes(int ng, int ext);
+// largest transform of a cell spectrum: 2 N_g + 2 at N_g = 6 with extended gridlets
+constexpr int kMaxCellC = 14;
 // the list of split parents that the cell-by-cell route visits is written by the tree build;
 // read_cell_parents takes its per-level bounds from the mailbox
 void read_cell_parents(Plan& p);

@@ -853,6 +853,7 @@ static TileTable tile_table(const Plan& p, int tile) {
 template <typename T, int NG, int EXT, bool SHARED = false>
 static void cells_t(Plan& p, hipStream_t s, hipEvent_t fork) {
   using S = CellShape<NG, EXT>;
+  static_assert(S::C <= kMaxCellC, "the Green table's kernel holds arrays of kMaxCellC per axis");
   p.m2l_split = SHARED || sizeof(T) == 4;
   p.m2l_mean_ff = false;  // this route's means are doubles
   if (p.nlevels <= 2) return;
@@ -927,7 +928,6 @@ static void cells_dispatch(Plan& p, hipStream_t s, hipEvent_t fork) {
     case 9: cells_t<T, 4, 1>(p, s, fork); break;
     case 12: cells_t<T, 6, 0>(p, s, fork); break;
     case 13: cells_t<T, 6, 1>(p, s, fork); break;
-    case 16: cells_t<T, 8, 0>(p, s, fork); break;
     default: fail(HPM_ERR_UNSUPPORTED, "no cell-by-cell kernels for this gridlet");
   }
 }

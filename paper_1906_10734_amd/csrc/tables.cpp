@@ -213,14 +213,14 @@ __global__ __launch_bounds__(kTableThreads) void k_green_xyz(GreenKernel g, Cosi
 }
 
 // Transform of the cyclic Green array of one source cube offset and level (grid: offsets, levels),
-// C <= 14: the kernel values and the y pass share one part of LDS, the x pass has the other.
-constexpr int kMaxC = 14, kMaxHC = 8;
+// C <= kMaxCellC: the kernel values and the y pass share one part of LDS, the x pass has the other.
 template <typename T>
 __global__ __launch_bounds__(kTableThreads) void k_green_cell(GreenKernel g, CellTrig tg, int ng, int ext,
                                                               int KP, T* gcell) {
 #pragma clang fp contract(off)
   __shared__ double s_c[16], s_s[16];
-  __shared__ double s_gv[2 * kMaxC * kMaxC * kMaxHC], s_a[2 * kMaxC * kMaxC * kMaxHC];
+  constexpr int kMaxModes = kMaxCellC * kMaxCellC * (kMaxCellC / 2 + 1);
+  __shared__ double s_gv[2 * kMaxModes], s_a[2 * kMaxModes];
   const int C = 2 * ng + 2 * ext, HC = C / 2 + 1, tid = threadIdx.x;
   const int od = blockIdx.x, li = blockIdx.y;
   const int d0 = od % 7 - 3, d1 = (od / 7) % 7 - 3, d2 = od / 49 - 3;
@@ -352,6 +352,7 @@ static void tables_t(Plan& p, int nlev, const Small& small, const Cosines& cs, c
     }
   }
   if (p.prob.m2l_mode != HPM_M2L_GRID) {
+    if (2 * ng + 2 * p.ext > kMaxCellC) fail(HPM_ERR_UNSUPPORTED, "no cell spectra for this gridlet");
     const int KP = int(cell_modes(ng, p.ext));
     t.gcell.reserve(size_t(std::max(nlev, 1)) * 343 * KP * 2 * sizeof(T));
     if (nlev > 0) {
