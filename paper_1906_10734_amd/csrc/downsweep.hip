@@ -832,8 +832,13 @@ __global__ __launch_bounds__(NT) void k_direct(int n, const T* x, const T* y, co
   if (threadIdx.x < TT * 4) {
     const int k = threadIdx.x / 4, q = threadIdx.x % 4;
     if (t0 + k < nt) {
-      double r = 0.0;
-      for (int v = 0; v < NW; ++v) r += s_red[v][k][q];
+      double r = 0.0, low = 0.0;  // compensated: 16 waves would add twice the rounding of 4
+      for (int v = 0; v < NW; ++v) {
+        double e;
+        two_sum(r, s_red[v][k][q], r, e);
+        low += e;
+      }
+      if (fabs(low) <= 1.7976931348623157e308) r += low;  // infinite sums have none
       const int i = targets[t0 + k];
       double* out = q == 0 ? phi : q == 1 ? ax : q == 2 ? ay : az;
       out[t0 + k] = i >= 0 && i < n ? G * r : __builtin_nan("");
