@@ -803,7 +803,9 @@ __global__ __launch_bounds__(NT) void k_direct(int n, const T* x, const T* y, co
     zi[k] = z[t[k]];
     p[k] = fx[k] = fy[k] = fz[k] = 0.0;
   }
-  for (int j = threadIdx.x; j < n; j += NT) {
+  // (a particle alone has no pair; its own, of mass 0, would still multiply an infinite distance)
+  const int sources = n > 1 ? n : 0;
+  for (int j = threadIdx.x; j < sources; j += NT) {
     const double xj = x[j], yj = y[j], zj = z[j], mj = m[j];
 #pragma unroll
     for (int k = 0; k < TT; ++k) {

@@ -41,3 +41,12 @@ def test_error_is_one_rounding(gen, nt):
     log(f"[direct accuracy] {gen.__name__} targets {nt}: phi {phi:.2e} acc {acc:.2e}")
     assert phi < 2.0 ** -53 and acc < 2.0 ** -51
 
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_a_particle_alone_feels_nothing(value):
+    import torch
+    from paper_1906_10734_amd import hpm
+    x = torch.full((1,), value, dtype=torch.float64, device="cuda")
+    y = torch.full_like(x, 0.5)
+    out = hpm.direct_sum(x, y, y, y, torch.tensor([0], device="cuda"))
+    assert all(float(v[0]) == 0.0 for v in out)
