@@ -125,9 +125,6 @@ static size_t projected_bytes(const Plan& p) {
   return p.device_bytes() + extra;
 }
 
-// particles from which the near zone of an execution runs beside the source-to-target step
-constexpr int64_t kForkMinParticles = int64_t(1) << 16;
-
 void rebuild_plan(Plan& p, int64_t n, const void* x, const void* y, const void* z, hipStream_t s) {
   p.valid = false;
   drain_tree(p);
@@ -234,7 +231,7 @@ void execute_plan(Plan& p, const void* m, void* phi, void* ax, void* ay, void* a
   // the near zone needs only the tree and the sorted masses: for large problems it runs on the
   // side stream beside the source-to-target step (which leaves ALU and memory slots idle) and
   // the leaf pass waits for it; small ones keep it in line, where the fork costs more than it hides
-  const bool fork = p.overlap && p.n >= kForkMinParticles && p.side;
+  const bool fork = p.near_beside();
   auto near_beside = [&] {
     HPM_HIP(hipStreamWaitEvent(p.side, p.fork_ev, 0));
     if (pev) HPM_HIP(hipEventRecord(pev[0], p.side));

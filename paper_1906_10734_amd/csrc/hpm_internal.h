@@ -142,6 +142,9 @@ struct Tables {
   int gcell_levels = 0;
 };
 
+// particles from which the near zone of an execution runs beside the source-to-target step
+constexpr int64_t kForkMinParticles = int64_t(1) << 16;
+
 struct Plan {
   hpm_problem prob{};
   int prec = HPM_F32;
@@ -256,6 +259,7 @@ struct Plan {
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool overlap = true;  // run the near zone on "side" (from kForkMinParticles particles on)
+  bool near_beside() const { return overlap && n >= kForkMinParticles && side; }
 
   // stage timing with HIP events (off unless enabled): a ring of pending executions
   static constexpr int kStages = 5;   // P2M, M2M, M2L, L2L, leaves

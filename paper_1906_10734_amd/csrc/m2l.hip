@@ -1092,12 +1092,17 @@ static void m2l_t(Plan& p, hipStream_t s) {
     p.m2l_mean_ff = true;
   }
   if constexpr (pair_kernel<T, NG>(0)) {
-    // Sibling pairs where they make at least two rounds of the resident workgroups; below, their
-    // longer items leave the chip short of work (Plummer sets, N_g = 6, FP32, us: 133 split parents
-    // 139 in pairs, 123 one by one; 267: 210, 204; 483: 316, 374. N_g = 4, FP64: 133: 98, 83; 483:
-    // 236, 268).
+    // Sibling pairs from 256 split parents (1024 items) on; below, their longer items leave the chip
+    // short of work. Evaluations of Plummer sets, time in pairs over time one by one, at 161, 250, 267
+    // (where the pairs begin a third round), 362 and 2048 parents: N_g = 4, FP32 1.02, 0.92, 0.97, 0.92,
+    // 0.86, FP64 1.06, 0.96, 1.00, 0.94, 0.93; N_g = 6, FP32 1.07, 0.94, 1.02, 0.92, 0.88, FP64 0.98,
+    // 0.88, 0.93, 0.86, 0.88; extended, FP32 at N_g = 4 and 6 1.04, 0.95, 1.00, 0.94, 0.90 and 1.00,
+    // 0.89, 0.95, 0.88, 0.84; FP64 at N_g = 4 1.05, 0.94, 0.99, 0.93, 0.93.
+    // The last one's pair kernel leaves no registers for the near zone's waves where that runs beside
+    // it (the kernel for one target does): 476 parents 1.08, 574 1.12, 746 1.05, 1033 1.00, 1435 0.96.
     const int nparents = p.cell_pbeg[p.nlevels - 1];
-    if (pair_kernel<T, NG>(p.ext) && int64_t(nparents) * 4 >= 2 * int64_t(p.m2l_slots)) {
+    const int enough = sizeof(T) == 8 && NG == 4 && p.ext && p.near_beside() ? 1024 : 256;
+    if (pair_kernel<T, NG>(p.ext) && nparents >= enough) {
       a.nparents = nparents;
       a.plist = p.cell_plist.as<int>();
       a.child8 = p.child8.as<int>();
