@@ -496,14 +496,24 @@ __device__ __forceinline__ void forward_slab(const M2LArgs<T>& a, const int* s_s
   __syncthreads();
 }
 
-// byte offsets of this thread's entries (folded ky, kx), e = tid + NT r, in a plane of the Green table
+// byte offsets of this thread's entries (folded ky, kx), e = tid + NT r, in a plane of the Green table.
+// N_g = 8, FP64: two to a register, and opaque so that they stay so; one to a register spilled 12 of
+// a thread's (2^16 Plummer, FP64: 4.45 ms with and without the spills; offsets formed anew at each use
+// 4.49).
 template <typename T, int NG, int EXT>
 __device__ __forceinline__ void green_offsets(uint32_t* goff) {
   using S = SlabShape<T, NG, EXT>;
 #pragma unroll
   for (int r = 0; r < S::PER; ++r) {
     const int e = int(threadIdx.x) + S::NT * r, ky = e / S::H, kx = e % S::H;
-    goff[r] = uint32_t((ky <= S::n / 2 ? ky : S::n - ky) * S::H + kx) * uint32_t(sizeof(T));
+    const uint32_t o = uint32_t((ky <= S::n / 2 ? ky : S::n - ky) * S::H + kx) * uint32_t(sizeof(T));
+    if constexpr (S::narrow) goff[r / 2] = r % 2 ? goff[r / 2] | (o << 16) : o;
+    else goff[r] = o;
+  }
+  if constexpr (S::narrow) {
+    static_assert(size_t(S::H) * S::H * sizeof(T) <= 65536, "an offset in 16 bits");
+#pragma unroll
+    for (int r = 0; r < (S::PER + 1) / 2; ++r) asm volatile("" : "+v"(goff[r]));
   }
 }
 
@@ -530,12 +540,13 @@ __device__ __forceinline__ void accumulate_slab(const cplx<T>* slab, const T* gt
       // offset: with the whole index formed per thread, 64-bit multiplies included, an entry took
       // 137 vector instructions instead of 95 (2^18 Plummer, N_g = 6, FP32: the kernel, bound by
       // vector issue, 1.75 -> 1.59 ms).
+      const uint32_t go = S::narrow ? (goff[r / 2] >> (r % 2 * 16)) & 0xffffu : goff[r];
       T g[NJ];
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const int d = Zt - z0 + j - (ZB - 1);
         const char* plane = reinterpret_cast<const char*>(gtab + size_t(d < 0 ? -d : d) * H * H);
-        g[j] = *reinterpret_cast<const T*>(plane + goff[r]);
+        g[j] = *reinterpret_cast<const T*>(plane + go);
       }
       cplx<T> sv[ZB];
 #pragma unroll
