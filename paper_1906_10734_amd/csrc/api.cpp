@@ -310,7 +310,9 @@ size_t plan_bytes_estimate(const hpm_problem& pr, int64_t n) {
                                                               // cubes, locals, fit rows
   b += c * (27 * 8 + 8 + 4 * (16 + 64 * 5 * s));  // near-zone ranges and work items
   const size_t H = 4 * ng + 1, levels = size_t(std::max(depth - 1, 1));
-  b += levels * (H * H * H + (4 * ng + 1) * H * H) * s;  // Green transforms
+  // Green transforms; the full octant is formed for N_g <= 3 only, and counted for every order: the
+  // estimate admits requests, and what it admits does not change with how the tables are kept
+  b += levels * (H * H * H + (4 * ng + 1) * H * H) * s;
   if (pr.m2l_mode != HPM_M2L_GRID) {
     const size_t spec = cell_modes(int(ng), pr.extended) * 2 * s;
     b += (2 * c + 1) * spec + levels * 343 * spec + 3 * 4 * c;

@@ -138,7 +138,6 @@ struct Tables {
                  // stored order of the cell spectra
   DevBuf twff;   // FP32 plans: [8 N_g] e^{+2 pi i m / n} as {cos hi, sin hi, cos lo, sin lo}
   int kpad = 0, mpad = 0;
-  int ghat_levels = 0;
   int gcell_levels = 0;
 };
 

@@ -405,7 +405,7 @@ struct SlabShape {
   static constexpr bool wide = NG >= 8;
   static constexpr bool narrow = wide && sizeof(T) == 8;
   static constexpr int ZB = wide ? (narrow ? 2 : NG / 2) : kSlabLayers * NG;  // source rows per slab
-  static constexpr int ZW = NL;                             // target z planes per pass
+  static constexpr int ZW = NL;                             // target z planes
   static constexpr int YS = narrow ? 4 : 1;                 // threads per forward y line
   static constexpr int XS = narrow ? 2 : 1;                 // threads per x line
   static constexpr int ZG = ZB < ZW ? ZB : ZW;              // planes per inverse-y group
@@ -421,11 +421,9 @@ struct SlabShape {
 };
 
 // The x and y transforms of the ZB source z rows from z0 on (of the cubes of s_src), into the slab buffer
-// [zb][ky][kx]. Called by all threads of the workgroup; ends with a barrier. tw holds
-// e^{+2 pi i m / n}, m < n.
+// [zb][ky][kx]. Called by all threads of the workgroup; ends with a barrier.
 template <typename T, int NG, int EXT>
-__device__ __forceinline__ void forward_slab(const M2LArgs<T>& a, const int* s_src, cplx<T>* slab, int z0,
-                                             const cplx<double>* tw) {
+__device__ __forceinline__ void forward_slab(const M2LArgs<T>& a, const int* s_src, cplx<T>* slab, int z0) {
   using S = SlabShape<T, NG, EXT>;
   constexpr int n = S::n, H = S::H, W = S::W, NT = S::NT, ZB = S::ZB, YS = S::YS;
   const int tid = threadIdx.x;
@@ -570,7 +568,7 @@ __device__ __forceinline__ void accumulate_slab(const cplx<T>* slab, const T* gt
 // The slab loop of the z-slab scheme: every source z row of the 6 N_g block (the cubes of s_src).
 template <typename T, int NG, int EXT = 0>
 __device__ __forceinline__ void slab_sum(const M2LArgs<T>& a, const int* s_src, cplx<T>* slab,
-                                         const T* gtab, int Zt, const cplx<double>* tw,
+                                         const T* gtab, int Zt,
                                          T (&pr)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
                                          T (&pi)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW]) {
   using S = SlabShape<T, NG, EXT>;
@@ -581,19 +579,19 @@ __device__ __forceinline__ void slab_sum(const M2LArgs<T>& a, const int* s_src, 
 #pragma unroll
     for (int zz = 0; zz < S::ZW; ++zz) pr[r][zz] = pi[r][zz] = T(0);
   for (int z0 = 0; z0 < S::W; z0 += S::ZB) {
-    forward_slab<T, NG, EXT>(a, s_src, slab, z0, tw);
+    forward_slab<T, NG, EXT>(a, s_src, slab, z0);
     accumulate_slab<T, NG, EXT>(slab, gtab, Zt, z0, goff, pr, pi);
     __syncthreads();
   }
 }
 
-// Inverse y transform of a pass's accumulated planes (all threads; the slab buffer takes ZG planes at
-// a time): red[Z][yy][kx] for the N_g target y values of octant half cy, the planes from zp on.
+// Inverse y transform of the accumulated planes (all threads; the slab buffer takes ZG planes at a time):
+// red[Z][yy][kx] for the N_g target y values of octant half cy.
 template <typename T, int NG, int EXT>
 __device__ __forceinline__ void inverse_y(const T (&pr)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
                                           const T (&pi)[SlabShape<T, NG, EXT>::PER][SlabShape<T, NG, EXT>::ZW],
                                           cplx<T>* slab, cplx<typename SlabShape<T, NG, EXT>::RedT>* red,
-                                          const cplx<double>* s_tw, int zp, int cy) {
+                                          const cplx<double>* s_tw, int cy) {
   using S = SlabShape<T, NG, EXT>;
   constexpr int n = S::n, H = S::H, NT = S::NT, PER = S::PER, ENT = S::ENT, ZW = S::ZW, ZG = S::ZG,
                 NL = S::NL;
@@ -624,7 +622,7 @@ __device__ __forceinline__ void inverse_y(const T (&pr)[SlabShape<T, NG, EXT>::P
 #pragma unroll
         for (int yy = 0; yy < NL; ++yy) {
           const cplx<T> o0 = out[2 * NG - EXT + yy], o1 = out[3 * NG - EXT + yy];
-          red[(size_t(zp + z0 + zz) * NL + yy) * H + kx] = {cy ? o1.re : o0.re, cy ? o1.im : o0.im};
+          red[(size_t(z0 + zz) * NL + yy) * H + kx] = {cy ? o1.re : o0.re, cy ? o1.im : o0.im};
         }
       }
     } else {
@@ -644,7 +642,7 @@ __device__ __forceinline__ void inverse_y(const T (&pr)[SlabShape<T, NG, EXT>::P
           mi += Y;
           if (mi >= n) mi -= n;
         }
-        red[(size_t(zp + z0 + zz) * NL + yy) * H + kx] = acc;
+        red[(size_t(z0 + zz) * NL + yy) * H + kx] = acc;
       }
     }
     __syncthreads();
@@ -758,7 +756,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
   using S = SlabShape<T, NG, EXT>;
   constexpr int n = S::n, H = S::H, NT = S::NT, D = S::D, PER = S::PER, ZW = S::ZW, NL = S::NL, ML = S::ML;
   static_assert(S::fits, "slab buffers exceed the LDS budget");
-  static_assert(S::W % S::ZB == 0 && S::W % 2 == 0 && NL % ZW == 0, "slab shape");
+  static_assert(S::W % S::ZB == 0 && S::W % 2 == 0 && NL == ZW, "slab shape");
   __shared__ int s_src[216];
   __shared__ int s_off[kMaxLevels + 1];
   __shared__ __align__(16) cplx<T> slab[S::ZB * n * H];  // [zb][ky (y before the y pass)][kx]
@@ -786,17 +784,14 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
     __syncthreads();
     const int Zt = __builtin_amdgcn_readfirstlane((2 + t.cz) * NG - EXT);
 
-    // The target z planes in passes of ZW (all N_g at once unless the accumulators would not
-    // fit), each pass's planes through the slab buffer ZG at a time for the inverse y transform.
-    // The inverse y transform runs in the plan's precision (the N_g target values of each column
-    // kept) and the inverse x transform in double precision as direct sums against a double
-    // twiddle table: the last rounding then happens at the magnitude of the potential's variation
-    // across the target, not at that of the interaction zone's large smooth potential.
-    for (int zp = 0; zp < NL; zp += ZW) {
-      T pr[PER][ZW], pi[PER][ZW];
-      slab_sum<T, NG, EXT>(a, s_src, slab, gtab, Zt + zp, s_tw, pr, pi);
-      inverse_y<T, NG, EXT>(pr, pi, slab, red, s_tw, zp, t.cy);
-    }
+    // All target z planes in one pass, then through the slab buffer ZG at a time for the inverse y
+    // transform, which runs in the plan's precision (the N_g target values of each column kept); the
+    // inverse x transform in double precision as direct sums against a double twiddle table: the
+    // last rounding then happens at the magnitude of the potential's variation across the target,
+    // not at that of the interaction zone's large smooth potential.
+    T pr[PER][ZW], pi[PER][ZW];
+    slab_sum<T, NG, EXT>(a, s_src, slab, gtab, Zt, pr, pi);
+    inverse_y<T, NG, EXT>(pr, pi, slab, red, s_tw, t.cy);
     inverse_x<T, NG, EXT, STRICT>(a, t.g, t.cx, red, s_tw, s_twf, s_out, s_red);
   }
 }
@@ -807,9 +802,11 @@ __global__ __launch_bounds__(kSlabThreads) void k_m2l_slab(M2LArgs<T> a) {
 // transforms of a layer for two targets instead of 12. What each target gets is, operation for
 // operation, what it would get alone: its layers' transforms in order, its own z sum and inverse.
 // The transforms are two thirds of the vector instructions that bound the kernel. 2^18 Plummer, N_g =
-// 6: FP32 1.59 -> 1.28 ms, FP64 3.39 -> 2.70 ms against one target at a time. Two workgroups per CU, as alone, although the
-// second accumulators then spill up to 40 registers of a thread (N_g = 4, FP64, 483 parents: 236 us, with
-// one workgroup per CU and no spills 322 us); with the extended gridlet at N_g = 6 one fits.
+// 6: FP32 1.59 -> 1.28 ms, FP64 3.39 -> 2.70 ms against one target at a time.
+// Two workgroups per CU, as alone, although the second accumulators then spill registers of a thread: 33
+// at N_g = 6 in FP32, 54 at N_g = 4 in FP64 (483 parents 236 us; with one workgroup per CU and no spills
+// 322 us), 162 there with the extended gridlet. At N_g = 6 in FP64 (LDS; 12 spilled) and extended in FP32
+// (registers) one workgroup fits.
 template <typename T, int NG, int EXT, bool STRICT = false>
 __global__ __launch_bounds__(kSlabThreads, (NG == 6 && (EXT || sizeof(T) == 8) ? 1 : 2)) void k_m2l_pair(M2LArgs<T> a) {
   using S = SlabShape<T, NG, EXT>;
@@ -864,18 +861,18 @@ __global__ __launch_bounds__(kSlabThreads, (NG == 6 && (EXT || sizeof(T) == 8) ?
       const bool use0 = kid0 >= 0 && (bz >= 1 && bz <= 3) == (near != 0);
       const bool use1 = kid1 >= 0 && (bz >= 2 && bz <= 4) == (near != 0);
       if (!use0 && !use1) continue;
-      forward_slab<T, NG, EXT>(a, s_src[near], slab, bz * NG, s_tw);
+      forward_slab<T, NG, EXT>(a, s_src[near], slab, bz * NG);
       if (use0) accumulate_slab<T, NG, EXT>(slab, gtab, 2 * NG - EXT, bz * NG, goff, pr0, pi0);
       if (use1) accumulate_slab<T, NG, EXT>(slab, gtab, 3 * NG - EXT, bz * NG, goff, pr1, pi1);
       __syncthreads();
     }
     if (kid0 >= 0) {
-      inverse_y<T, NG, EXT>(pr0, pi0, slab, red, s_tw, 0, cy);
+      inverse_y<T, NG, EXT>(pr0, pi0, slab, red, s_tw, cy);
       inverse_x<T, NG, EXT, STRICT>(a, kid0, cx, red, s_tw, s_twf, s_out, s_red);
       __syncthreads();  // red, s_out and s_red are reused
     }
     if (kid1 >= 0) {
-      inverse_y<T, NG, EXT>(pr1, pi1, slab, red, s_tw, 0, cy);
+      inverse_y<T, NG, EXT>(pr1, pi1, slab, red, s_tw, cy);
       inverse_x<T, NG, EXT, STRICT>(a, kid1, cx, red, s_tw, s_twf, s_out, s_red);
     }
   }
@@ -886,11 +883,11 @@ __global__ __launch_bounds__(kSlabThreads, (NG == 6 && (EXT || sizeof(T) == 8) ?
 // in the parent's 6^3 block; the 152 block cubes outside the central 4^3 are in the zone of all
 // 8 children. One workgroup per parent runs the z-slab scheme over those cubes for both halves cz
 // of the children at once (target z windows (2 + cz) N_g .. (3 + cz) N_g - 1, each with its own
-// accumulators), then for each half
-// the inverse y transform keeping both children's y windows, then for each existing child the
-// inverse x transform, its mean and its zero-mean gridlet. The other 37 cubes of each child's zone
-// are added afterwards, cell by cell. 2^18 Plummer, N_g = 6, FP32: 0.49 ms with the halves one after
-// the other, each with its own x and y transforms, 0.36 ms at once.
+// accumulators), then for each half the inverse y transform keeping both children's y windows, then for
+// each existing child the inverse x transform, its mean and its zero-mean gridlet. The other 37 cubes of
+// each child's zone are added afterwards, cell by cell. 2^18 Plummer, N_g = 6, FP32: 0.49 ms with the
+// halves one after the other, each with its own x and y transforms, 0.36 ms at once, although the second
+// accumulators spill 38 registers of a thread (FP64: 49 at N_g = 4, 12 at N_g = 6).
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NG>
 struct ParentShape {
@@ -904,7 +901,7 @@ template <typename T, int NG>
 __global__ __launch_bounds__(kSlabThreads, (sizeof(T) == 4 || NG <= 4 ? 2 : 1)) void k_m2l_parent(M2LArgs<T> a) {
   using S = SlabShape<T, NG>;
   constexpr int n = S::n, H = S::H, M = S::M, NT = S::NT, D = S::D, PER = S::PER, ENT = S::ENT;
-  constexpr int NW = 2;  // z windows per pass
+  constexpr int NW = 2;  // z windows
   static_assert(ParentShape<T, NG>::fits, "parent buffers exceed the LDS budget");
   static_assert(S::ZB >= NG, "the slab buffer holds the N_g accumulated planes");
   __shared__ int s_src[216];
@@ -942,94 +939,91 @@ __global__ __launch_bounds__(kSlabThreads, (sizeof(T) == 4 || NG <= 4 ? 2 : 1)) 
     __syncthreads();
     const T* gtab = a.gxy + size_t(__builtin_amdgcn_readfirstlane(l) - 2) * D * H * H;
 
-    // the children's two z windows, NW at a time from the same x and y transforms
-    for (int cz0 = 0; cz0 < 2; cz0 += NW) {
-      // block-uniform: every thread reads the same child ids
-      bool want[NW];
-      bool any = false;
+    // the children's two z windows from the same x and y transforms
+    // block-uniform: every thread reads the same child ids
+    bool want[NW];
+    bool any = false;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int* kid = s_kid + 4 * (cz0 + w);
-        want[w] = __builtin_amdgcn_readfirstlane(int(kid[0] >= 0 || kid[1] >= 0 || kid[2] >= 0 || kid[3] >= 0));
-        any = any || want[w];
-      }
-      if (!any) continue;
-      T pr[NW][PER][NG], pim[NW][PER][NG];
+    for (int w = 0; w < NW; ++w) {
+      const int* kid = s_kid + 4 * w;
+      want[w] = __builtin_amdgcn_readfirstlane(int(kid[0] >= 0 || kid[1] >= 0 || kid[2] >= 0 || kid[3] >= 0));
+      any = any || want[w];
+    }
+    if (!any) continue;
+    T pr[NW][PER][NG], pim[NW][PER][NG];
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int r = 0; r < PER; ++r)
+#pragma unroll
+        for (int zz = 0; zz < NG; ++zz) pr[w][r][zz] = pim[w][r][zz] = T(0);
+    for (int z0 = 0; z0 < S::W; z0 += S::ZB) {
+      forward_slab<T, NG, 0>(a, s_src, slab, z0);
 #pragma unroll
       for (int w = 0; w < NW; ++w)
+        if (want[w]) accumulate_slab<T, NG, 0>(slab, gtab, (2 + w) * NG, z0, goff, pr[w], pim[w]);
+      __syncthreads();
+    }
 #pragma unroll
-        for (int r = 0; r < PER; ++r)
+    for (int win = 0; win < NW; ++win) {
+      if (!want[win]) continue;
 #pragma unroll
-          for (int zz = 0; zz < NG; ++zz) pr[w][r][zz] = pim[w][r][zz] = T(0);
-      for (int z0 = 0; z0 < S::W; z0 += S::ZB) {
-        forward_slab<T, NG, 0>(a, s_src, slab, z0, s_tw);
+      for (int r = 0; r < PER; ++r) {
+        const int e = tid + NT * r;
+        if (e < ENT) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
-          if (want[w]) accumulate_slab<T, NG, 0>(slab, gtab, (2 + cz0 + w) * NG, z0, goff, pr[w], pim[w]);
-        __syncthreads();
+          for (int zz = 0; zz < NG; ++zz) slab[size_t(zz) * ENT + e] = {pr[win][r][zz], pim[win][r][zz]};
+        }
       }
+      __syncthreads();
+      // y^-1: red[Z][Y][kx], Y = 2 N_g + yy for yy < 2 N_g (the windows of cy = 0 and 1)
+      for (int w = tid; w < NG * H; w += NT) {
+        const int kx = w % H, zz = w / H;
+        const cplx<T>* col = slab + size_t(zz) * ENT + kx;
+        cplx<T> in[n], out[n];
 #pragma unroll
-      for (int win = 0; win < NW; ++win) {
-        if (!want[win]) continue;
-        const int cz = cz0 + win;
+        for (int y = 0; y < n; ++y) in[y] = col[size_t(y) * H];
+        fft<n, +1>(in, out);
 #pragma unroll
-        for (int r = 0; r < PER; ++r) {
-          const int e = tid + NT * r;
-          if (e < ENT) {
-#pragma unroll
-            for (int zz = 0; zz < NG; ++zz) slab[size_t(zz) * ENT + e] = {pr[win][r][zz], pim[win][r][zz]};
+        for (int yy = 0; yy < 2 * NG; ++yy) red[(size_t(zz) * 2 * NG + yy) * H + kx] = out[2 * NG + yy];
+      }
+      __syncthreads();
+      for (int c = 4 * win; c < 4 * win + 4; ++c) {
+        const int g = s_kid[c];
+        if (g < 0) continue;  // block-uniform
+        const int cx = c & 1, cy = (c >> 1) & 1;
+        // x^-1 (Hermitian half spectrum) in double: out = sum_k w_k Re(F_k e^{+2 pi i k X / n}),
+        // w_k = 1 at k = 0 and n/2, 2 otherwise; X = (2 + c_x) N_g + xx
+        const int Xt = (2 + cx) * NG;
+        for (int q = tid; q < M; q += NT) {
+          const int xx = q % NG, yy = (q / NG) % NG, zz = q / (NG * NG);
+          const int X = Xt + xx;
+          const cplx<T>* F = red + (size_t(zz) * 2 * NG + cy * NG + yy) * H;
+          double acc = 0.0;
+          int m = 0;
+          for (int k = 0; k < H; ++k) {
+            const cplx<double> f = {double(F[k].re), double(F[k].im)};
+            const cplx<double> w = s_tw[m];
+            const double v = f.re * w.re - f.im * w.im;
+            acc += (k == 0 || k == n / 2) ? v : 2.0 * v;
+            m += X;
+            if (m >= n) m -= n;
           }
+          s_out[q] = acc;
         }
         __syncthreads();
-        // y^-1: red[Z][Y][kx], Y = 2 N_g + yy for yy < 2 N_g (the windows of cy = 0 and 1)
-        for (int w = tid; w < NG * H; w += NT) {
-          const int kx = w % H, zz = w / H;
-          const cplx<T>* col = slab + size_t(zz) * ENT + kx;
-          cplx<T> in[n], out[n];
-#pragma unroll
-          for (int y = 0; y < n; ++y) in[y] = col[size_t(y) * H];
-          fft<n, +1>(in, out);
-#pragma unroll
-          for (int yy = 0; yy < 2 * NG; ++yy) red[(size_t(zz) * 2 * NG + yy) * H + kx] = out[2 * NG + yy];
-        }
+        double part = 0.0;
+        for (int e = tid; e < M; e += NT) part += s_out[e];
+        part = wave_sum(part);
+        if ((tid & 63) == 0) s_red[tid >> 6] = part;
         __syncthreads();
-        for (int c = 4 * cz; c < 4 * cz + 4; ++c) {
-          const int g = s_kid[c];
-          if (g < 0) continue;  // block-uniform
-          const int cx = c & 1, cy = (c >> 1) & 1;
-          // x^-1 (Hermitian half spectrum) in double: out = sum_k w_k Re(F_k e^{+2 pi i k X / n}),
-          // w_k = 1 at k = 0 and n/2, 2 otherwise; X = (2 + c_x) N_g + xx
-          const int Xt = (2 + cx) * NG;
-          for (int q = tid; q < M; q += NT) {
-            const int xx = q % NG, yy = (q / NG) % NG, zz = q / (NG * NG);
-            const int X = Xt + xx;
-            const cplx<T>* F = red + (size_t(zz) * 2 * NG + cy * NG + yy) * H;
-            double acc = 0.0;
-            int m = 0;
-            for (int k = 0; k < H; ++k) {
-              const cplx<double> f = {double(F[k].re), double(F[k].im)};
-              const cplx<double> w = s_tw[m];
-              const double v = f.re * w.re - f.im * w.im;
-              acc += (k == 0 || k == n / 2) ? v : 2.0 * v;
-              m += X;
-              if (m >= n) m -= n;
-            }
-            s_out[q] = acc;
-          }
-          __syncthreads();
-          double part = 0.0;
-          for (int e = tid; e < M; e += NT) part += s_out[e];
-          part = wave_sum(part);
-          if ((tid & 63) == 0) s_red[tid >> 6] = part;
-          __syncthreads();
-          double mean = 0.0;
+        double mean = 0.0;
 #pragma unroll
-          for (int w = 0; w < NT / 64; ++w) mean += s_red[w];
-          mean *= 1.0 / M;
-          for (int e = tid; e < M; e += NT) a.local[size_t(g) * M + e] = T(s_out[e] - mean);
-          if (tid == 0) a.m2l_mean[g] = mean;
-          __syncthreads();  // s_out and s_red are reused by the next child
-        }
+        for (int w = 0; w < NT / 64; ++w) mean += s_red[w];
+        mean *= 1.0 / M;
+        for (int e = tid; e < M; e += NT) a.local[size_t(g) * M + e] = T(s_out[e] - mean);
+        if (tid == 0) a.m2l_mean[g] = mean;
+        __syncthreads();  // s_out and s_red are reused by the next child
       }
     }
   }

@@ -52,7 +52,7 @@ template <int NG, int EXT>
 struct CellShape {
   static constexpr int C = 2 * NG + 2 * EXT;
   static constexpr int HC = C / 2 + 1;
-  static constexpr int K = C * C * HC;      // modes, [kz][ky][kx]
+  static constexpr int K = C * C * HC;      // modes, [ky][kx][kz]
   static constexpr int KP = (K + 15) / 16 * 16;  // stored row: K modes, then zeros
   static constexpr int M = NG * NG * NG;    // source gridlet
   static constexpr int NL = NG + 2 * EXT;   // target gridlet nodes per axis

@@ -4,7 +4,8 @@
 // kernels below by value; they form the tables in place. A plan's creation pays for them: on the
 // host they took 2.3 of the 3.5 ms of a one-shot solve of 3000 particles at N_g = 4, and 0.1 s of a
 // plan with cell spectra at N_g = 6; here they are four launches with no copy and no wait. Sums run
-// in index order without contraction, as they did there, so the values are the same.
+// in index order without contraction, as they did there, so the values are the same; those of the
+// screened kernel up to the last bit of the device's exp.
 //
 //   fit matrix   Effective masses from moments (Sec. 2.2, Eq. 4-5). The moments here are taken
 //                in the tensor Legendre basis phi_n(x) = P_nx(2x) P_ny(2y) P_nz(2z), which spans
@@ -402,7 +403,6 @@ void build_tables(Plan& p, int max_levels, hipStream_t s) {
   }
   // Green transforms of levels 2 .. nlevels-1
   const int nlev = std::max(0, max_levels - 2);
-  p.tab.ghat_levels = nlev;
   if (p.prec == HPM_F32) tables_t<float>(p, nlev, small, cs, tg, s);
   else tables_t<double>(p, nlev, small, cs, tg, s);
 }
