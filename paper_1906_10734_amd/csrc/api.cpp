@@ -242,13 +242,14 @@ void execute_plan(Plan& p, const void* m, void* phi, void* ax, void* ay, void* a
   if (fork) HPM_HIP(hipEventRecord(p.fork_ev, s));
   // On the cell and shared routes it starts behind the source spectra and is launched after the
   // products, whose few large workgroups then find their compute units free: from the start, the
-  // near zone's small ones sat on some of them and the products ran unevenly (cells, N_g = 6, FP64:
-  // 100,003 Plummer particles 867 -> 700 us an evaluation, in line 806; 2^18 1.58 -> 1.45 ms; FP32
-  // 439 -> 406 us and 0.88 -> 0.84; shared, FP64, 2^18 1.88 -> 1.71; equal within 1% from 10^6 FP32
-  // particles on). It keeps the early start on the shared route at N_g = 6 in FP32, where the
-  // per-parent kernel would share the chip with it (0.99 ms, 1.18 late), and for N_g <= 3 in FP64 or
-  // on the shared route, where the near zone is the longer part (66,000 particles, N_g = 2: 244 us,
-  // 259 late).
+  // near zone's small ones sit on some of them and the products run unevenly. Evaluations of 66,000 to
+  // 10^6 Plummer, clustered and uniform particles, time late over time early: cells, N_g = 4 and 6,
+  // with and without extended gridlets, FP32 0.81 .. 1.00, FP64 0.74 .. 1.01; shared, N_g = 4, FP32 0.95 ..
+  // 1.01, FP64 0.93 .. 0.99, N_g = 6, FP64 0.91 .. 0.97. It keeps the early start on the shared route at
+  // N_g = 6 in FP32, where the per-parent kernel would share the chip with it (2^18 Plummer 1.19, up to
+  // 1.28), and for N_g <= 3 where the near zone is the longer part of a small set: shared, FP32 0.95 ..
+  // 1.06, FP64 0.95 .. 1.05; cells, FP64, 1.01 .. 1.09 at 66,000 to 100,003 particles, 0.75 .. 1.00 from
+  // 131,072. Cells in FP32 start late there too: 0.83 .. 1.05 up to 131,072, 0.90 .. 1.00 above.
   const bool late = p.route == HPM_M2L_CELLS    ? p.prec == HPM_F32 || p.ng > 3
                     : p.route == HPM_M2L_SHARED ? p.ng > 3 && !(p.prec == HPM_F32 && p.ng == 6)
                                                 : false;
