@@ -1105,9 +1105,17 @@ static void m2l_t(Plan& p, hipStream_t s) {
     // 0.89, 0.95, 0.88, 0.84; FP64 at N_g = 4 1.05, 0.94, 0.99, 0.93, 0.93.
     // The last one's pair kernel leaves no registers for the near zone's waves where that runs beside
     // it (the kernel for one target does): 476 parents 1.08, 574 1.12, 746 1.05, 1033 1.00, 1435 0.96.
+    // And only where most siblings exist: a target whose partner is missing costs a whole item. On trees of
+    // 2.7, 4.2, 5.2, 5.8, 6.4, 6.9 and 7.7 children per split parent: N_g = 4, FP32 2.02, 1.22, 1.26, 1.13,
+    // 0.98, 0.97, 0.88, FP64 2.12, 1.27, 1.28, 1.15, 1.03, 1.00, 0.91; N_g = 6, FP32 2.02, 1.24, 1.26,
+    // 1.13, 0.99, 0.98, 0.90, FP64 1.96, 1.14, 1.19, 1.06, 0.96, 0.92, 0.84; extended, FP32 at N_g = 4 2.00,
+    // 1.24, 1.27, 1.15, 1.01, 1.01, 0.92, at N_g = 6 2.03, 1.17, 1.25, 1.11, 1.01, 0.96, 0.87, FP64 at N_g =
+    // 4 2.14, 1.26, 1.30, 1.18, 1.03, 1.02, 0.93.
     const int nparents = p.cell_pbeg[p.nlevels - 1];
     const int enough = sizeof(T) == 8 && NG == 4 && p.ext && p.near_beside() ? 1024 : 256;
-    if (pair_kernel<T, NG>(p.ext) && nparents >= enough) {
+    const int tenths = p.ext ? 69 : NG == 6 && sizeof(T) == 8 ? 60 : 65;  // children per parent
+    const bool full = 10 * int64_t(a.ntargets) >= tenths * int64_t(nparents);
+    if (pair_kernel<T, NG>(p.ext) && nparents >= enough && full) {
       a.nparents = nparents;
       a.plist = p.cell_plist.as<int>();
       a.child8 = p.child8.as<int>();
