@@ -201,37 +201,26 @@ __global__ __launch_bounds__(256) void k_fit_gemm(const T* __restrict__ Q, const
   }
 }
 
-// One workgroup per split cell of the level (from the list of split cells). The passes take all 8
-// children at once, three barriers instead of four per child; each child's result and the order of
-// their sum are those of a loop over the children. 2^24 clustered particles, N_g = 4, FP32: 0.94 ms
-// with a workgroup per cell and a child at a time, 0.34 ms; on small trees the chain of launches is
-// latency (2^18 Plummer, N_g = 6: six launches of 9.0, now 7.9 us).
-template <typename T, int NG>
-__global__ __launch_bounds__(256) void k_m2m(const int* __restrict__ split, const int* __restrict__ child8,
-                                             const T* __restrict__ t1, T* __restrict__ gridlet) {
+// The child gridlets of s_ch, in the octants s_oct, "count" of them (FULL: all 8, child c in octant c),
+// carried to the parent's nodes and added up in order.
+template <typename T, int NG, bool FULL>
+__device__ __forceinline__ void m2m_children(int count, const int* s_ch, const int* s_oct, const T (&s_t)[2][NG][NG],
+                                             T* s_in, T* s_a, T* gridlet, int g) {
   constexpr int M = NG * NG * NG;
-  __shared__ T s_in[8 * M], s_a[8 * M];
-  __shared__ T s_t[2][NG][NG];
-  __shared__ int s_ch[8];
-  const int g = split[blockIdx.x], tid = threadIdx.x;
-  if (tid < 8) s_ch[tid] = child8[size_t(g) * 8 + tid];
-  for (int e = tid; e < 2 * NG * NG; e += 256) (&s_t[0][0][0])[e] = t1[e];
+  const int tid = threadIdx.x, nc = FULL ? 8 : count;
+  auto oct = [&](int k) { return FULL ? k : s_oct[k]; };
+  for (int e = tid; e < nc * M; e += 256) s_in[e] = gridlet[size_t(s_ch[e / M]) * M + e % M];
   __syncthreads();
-  for (int e = tid; e < 8 * M; e += 256) {
-    const int ch = s_ch[e / M];
-    s_in[e] = ch >= 0 ? gridlet[size_t(ch) * M + e % M] : T(0);
-  }
-  __syncthreads();
-  for (int e = tid; e < 8 * M; e += 256) {  // [child][qz][qy][px]
-    const int px = e % NG, rest = e / NG, ax = (e / M) & 1;
+  for (int e = tid; e < nc * M; e += 256) {  // [child][qz][qy][px]
+    const int px = e % NG, rest = e / NG, ax = oct(e / M) & 1;
     T acc = T(0);
 #pragma unroll
     for (int q = 0; q < NG; ++q) acc += s_t[ax][px][q] * s_in[rest * NG + q];
     s_a[e] = acc;
   }
   __syncthreads();
-  for (int e = tid; e < 8 * M; e += 256) {  // [child][qz][py][px]
-    const int px = e % NG, py = (e / NG) % NG, cz = e / (NG * NG), ay = (e / (2 * M)) & 1;
+  for (int e = tid; e < nc * M; e += 256) {  // [child][qz][py][px]
+    const int px = e % NG, py = (e / NG) % NG, cz = e / (NG * NG), ay = (oct(e / M) >> 1) & 1;
     T acc = T(0);
 #pragma unroll
     for (int q = 0; q < NG; ++q) acc += s_t[ay][py][q] * s_a[(cz * NG + q) * NG + px];
@@ -241,16 +230,49 @@ __global__ __launch_bounds__(256) void k_m2m(const int* __restrict__ split, cons
   for (int e = tid; e < M; e += 256) {
     const int pxy = e % (NG * NG), pz = e / (NG * NG);
     T out = T(0);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      if (s_ch[c] < 0) continue;
+    auto add = [&](int c) {
+      const int az = oct(c) >> 2;
       T acc = T(0);
 #pragma unroll
-      for (int q = 0; q < NG; ++q) acc += s_t[c >> 2][pz][q] * s_in[(c * NG + q) * NG * NG + pxy];
+      for (int q = 0; q < NG; ++q) acc += s_t[az][pz][q] * s_in[(c * NG + q) * NG * NG + pxy];
       out += acc;
+    };
+    if constexpr (FULL) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) add(c);
+    } else {
+      for (int c = 0; c < nc; ++c) add(c);
     }
     gridlet[size_t(g) * M + e] = out;
   }
+}
+
+// One workgroup per split cell of the level (from the list of split cells). The passes take all the
+// children at once, three barriers instead of four per child; each child's result and the order of
+// their sum are those of a loop over the children. 2^24 clustered particles, N_g = 4, FP32: 0.94 ms
+// with a workgroup per cell and a child at a time, 0.34 ms; on small trees the chain of launches is
+// latency (2^18 Plummer, N_g = 6: launches of 9.0, now 8.5 us in the mean). Cells without all 8 pass
+// over the absent ones: with zeros in their places, trees whose cells have one or two children (172 to
+// 189 cells, N_g = 6, FP32) took 5.7 us a launch, 4.9 without, 4.7 a child at a time.
+template <typename T, int NG>
+__global__ __launch_bounds__(256) void k_m2m(const int* __restrict__ split, const int* __restrict__ child8,
+                                             const T* __restrict__ t1, T* __restrict__ gridlet) {
+  constexpr int M = NG * NG * NG;
+  __shared__ T s_in[8 * M], s_a[8 * M];
+  __shared__ T s_t[2][NG][NG];
+  __shared__ int s_ch[8], s_oct[8];
+  const int g = split[blockIdx.x], tid = threadIdx.x, lane = tid & 63;
+  const int ch = lane < 8 ? child8[size_t(g) * 8 + lane] : -1;
+  const uint64_t have = __ballot(ch >= 0);
+  if (tid < 8 && ch >= 0) {
+    const int k = __popcll(have & ((1ull << tid) - 1));
+    s_ch[k] = ch;
+    s_oct[k] = tid;
+  }
+  for (int e = tid; e < 2 * NG * NG; e += 256) (&s_t[0][0][0])[e] = t1[e];
+  __syncthreads();
+  if (have == 255) m2m_children<T, NG, true>(8, s_ch, s_oct, s_t, s_in, s_a, gridlet, g);
+  else m2m_children<T, NG, false>(__popcll(have), s_ch, s_oct, s_t, s_in, s_a, gridlet, g);
 }
 
 static inline int nblk(int64_t n, int t) { return int((n + t - 1) / t); }
