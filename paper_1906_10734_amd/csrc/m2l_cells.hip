@@ -284,8 +284,9 @@ struct AccumShape {
 // once.
 //
 // Measured per evaluation, near zone in line, against one thread per (parent, mode) on the vector
-// ALU, one launch per level: 2^24 clustered particles (N_g = 4, FP32) 21.1 -> 14.0 ms (70 TFLOP/s of
-// matrix work, 49% of the cycles); 10^6 clustered, extended N_g = 6, FP32 3.73 -> 2.27 ms; 150,001
+// ALU, one launch per level: 2^24 clustered particles (N_g = 4, FP32) 21.1 -> 14.2 ms (68 TFLOP/s of
+// matrix work; the matrix cores busy 43% of the time at 2.4 GHz, 58% of the cycles at the clock the chip
+// then runs); 10^6 clustered, extended N_g = 6, FP32 3.73 -> 2.27 ms; 150,001
 // Plummer, N_g = 6, FP64 0.96 -> 0.52 ms; the central cubes of 2^18 Plummer, N_g = 6, FP32
 // 0.31 -> 0.20 ms. With every source row in L2 the 2^24 case takes 13.2 ms (measured on the version
 // before the operand pipeline): what bounds it is issue beside the matrix instructions, two waves
